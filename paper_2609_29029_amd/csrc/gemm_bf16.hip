@@ -6,16 +6,15 @@
 //   RESID x += A B^T in float32 (attention output and FFN down projections)
 //   SWIGLU a = silu(h wg^T) * (h wu^T), bf16 out
 //
-// Tiling: a 256x256 output tile per workgroup of 8 waves (2 in M x 4 in N),
-// each wave a 128x64 block of 8x4 v_mfma_f32_16x16x32_bf16 tiles (under the
-// board power limit this instruction sustains more throughput than the
-// 32x32x16 form on the same data).  K advances 64 per stage through two LDS
-// buffers of 64 KB that LDS DMA (global_load_lds) fills a stage ahead.  The
-// whole tiles run the ping-pong loop (the two waves on a SIMD alternate
-// between a whole stage of MFMAs and the LDS reads of the next stage); the
-// last tiles of a GEMM can run as 256x128 halves on 4 waves, each of which
-// reads its operands for the next 32-deep sub-step while it runs the MFMAs of
-// the current one.
+// Tiling: a tile of 32 MB rows (MB = 5..8) x 256 columns per workgroup of 8
+// waves (2 in M x 4 in N), each wave a block of MB x 4
+// v_mfma_f32_16x16x32_bf16 tiles (under the board power limit this instruction
+// sustains more throughput than the 32x32x16 form on the same data).  K advances
+// 64 per stage through two LDS buffers that LDS DMA (global_load_lds) fills a
+// stage ahead; the two waves on a SIMD alternate between a whole stage of MFMAs
+// and the LDS reads of the next stage (ping-pong).  Products with few rows, and
+// the last tiles of a GEMM where that is cheaper, run as short tiles of 32 to
+// 128 rows x 128 columns on 4 waves (plan_gemm chooses).
 //
 // Every output element is one fixed sequence of MFMA accumulations over K, no
 // matter which tile or batch row holds it, so a row's result does not depend on
@@ -38,7 +37,6 @@ namespace rift {
 
 namespace {
 
-constexpr int BM = 256;
 constexpr int BN = 256;
 constexpr int kGroupM = 8;
 
@@ -97,12 +95,6 @@ __device__ __forceinline__ void group_coords(int t, int num_m, int num_n, int& b
     bn = in_group / gm;
 }
 
-// B operand of tile bn, row r (0..255): b_base_row is the matrix it is read
-// from and b_row the row inside that matrix.
-//   QKV:    one of wq | wk | wv per tile (d % 256 == 0), row bn*256 + r - region*d
-//   SWIGLU: tile rows [0,64) gate, [64,128) up for output columns bn*128 + [0,64),
-//           rows [128,192) gate, [192,256) up for columns bn*128 + [64,128)
-//   RESID:  row bn*256 + r
 // One of three pointers by a wave-uniform index, as selects on values (an
 // indexed read of the kernel-argument struct would put it in scratch memory).
 template <typename T>
@@ -113,11 +105,17 @@ __device__ __forceinline__ T* pick3(int i, T* x, T* y, T* z) {
     return (T*)r;
 }
 
+// B operand of the tile whose first column is n0 (a multiple of 128), tile row
+// r: b_base is the matrix it is read from and b_row the row inside that matrix.
+//   QKV:    one of wq | wk | wv per tile (d % 256 == 0), row n0 + r - region d
+//   SWIGLU: rows [0, 64) gate, [64, 128) up for output columns n0 / 2 + [0, 64),
+//           and of a 256-column tile rows [128, 192) gate, [192, 256) up for
+//           columns n0 / 2 + [64, 128)
+//   RESID:  row n0 + r
 template <int EPI>
-__device__ __forceinline__ const bf16_t* b_base_row(const GemmParams& p, int bn, int r) {
+__device__ __forceinline__ const bf16_t* b_base(const GemmParams& p, int n0, int r) {
     if constexpr (EPI == EPI_QKV) {
-        const int region = __builtin_amdgcn_readfirstlane((bn * BN) / p.d);
-        return pick3(region, p.b0, p.b1, p.b2);
+        return pick3(__builtin_amdgcn_readfirstlane(n0 / p.d), p.b0, p.b1, p.b2);
     } else if constexpr (EPI == EPI_SWIGLU) {
         return ((r & 127) < 64) ? p.b0 : p.b1;
     } else {
@@ -126,14 +124,13 @@ __device__ __forceinline__ const bf16_t* b_base_row(const GemmParams& p, int bn,
 }
 
 template <int EPI>
-__device__ __forceinline__ int b_row(const GemmParams& p, int bn, int r) {
+__device__ __forceinline__ int b_row(const GemmParams& p, int n0, int r) {
     if constexpr (EPI == EPI_QKV) {
-        const int region = (bn * BN) / p.d;
-        return bn * BN + r - region * p.d;
+        return n0 + r - (n0 / p.d) * p.d;
     } else if constexpr (EPI == EPI_SWIGLU) {
-        return bn * 128 + (r >> 7) * 64 + (r & 63);
+        return (n0 >> 1) + (r >> 7) * 64 + (r & 63);
     } else {
-        return bn * BN + r;
+        return n0 + r;
     }
 }
 
@@ -151,18 +148,18 @@ __device__ __forceinline__ void dma16s(const void* base, uint32_t voff, uint32_t
 __device__ __forceinline__ void wg_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
 // ---------------------------------------------------------------------------
-// Stages are 64 deep: two LDS buffers of 64 KB (A and B tiles, rows of 128
+// Stages are 64 deep (A and B tiles, rows of 128
 // bytes = one cache line of a K-contiguous operand row, so every LDS DMA
 // request reads whole lines).  LDS rows hold 8 chunks of 16 bytes; chunk c of
 // row r sits at c ^ swz8(r), conflict-free for the operand reads.
 constexpr int BK3 = 64;
-constexpr int kStage3 = 2 * BM * BK3;   // elements per stage (A then B)
 
 __device__ __forceinline__ int swz8(int r) { return ((r >> 1) ^ ((r & 1) << 2)) & 7; }
 
 // ---------------------------------------------------------------------------
-// Wave layout: 2 (M) x 4 (N) waves, each 128 rows x 64 columns: eight 16-row
-// blocks mb and four 16-column blocks nb at tile columns
+// Wave layout: 2 (M) x 4 (N) waves (2 x 2 in the short-tile kernel), each 16 MB
+// rows x 64 columns: MB 16-row blocks mb and four 16-column blocks nb at tile
+// columns
 // c0 + 16 (nb & 1) + 64 (nb >> 1) with c0 = 128 (wn >> 1) + 32 (wn & 1), so the
 // RoPE pairs (j, j + 64) of a head and the gate/up pairs of SwiGLU (blocks nb
 // and nb + 2) sit in the same lane.
@@ -185,38 +182,37 @@ __device__ __forceinline__ int snake_nb(int i) { return ((i >> 2) & 1) ? 3 - (i 
 // into a row-major tile in LDS, then every thread of the workgroup moves 16
 // contiguous bytes of a row, so global stores are whole row segments.  The
 // residual GEMMs read, add and write float32 straight from the lanes (16
-// consecutive columns of 4 rows per instruction).  acc[mb][nb][v] is tile row
-// 128 wm + 16 mb + 4 (lane/16) + v, tile column w8_col(wn, nb) + lane%16.  A
-// half-tile workgroup (HALF) holds logical tile columns [128 h, 128 h + 128).
-constexpr int kStagingBytes = 256 * (256 + 8) * 2;   // largest staging tile (QKV, bf16)
-
-template <int EPI, bool HALF>
-__device__ __forceinline__ void epilogue_staged(const GemmParams& p, f32x4_t (&acc)[8][4], int m0, int bn,
-                                                int h, int wm, int wn, int lane, const int* pos_lds,
-                                                unsigned char* stage) {
-    constexpr int NT = HALF ? 256 : 512;
+// consecutive columns of 4 rows per instruction).  The tile is 32 MB rows from
+// m0 and COLS (256, or 128 in the short-tile kernel) columns from n0;
+// acc[mb][nb][v] is tile row 16 MB wm + 16 mb + 4 (lane/16) + v, tile column
+// w8_col(wn, nb) + lane%16.
+template <int EPI, int MB, int COLS>
+__device__ __forceinline__ void epilogue_staged(const GemmParams& p, f32x4_t (&acc)[MB][4], int m0, int n0, int wm,
+                                                int wn, int lane, const int* pos_lds, unsigned char* stage) {
+    constexpr int NT = 2 * COLS;
+    constexpr int ROWS = 32 * MB;
     const int tid = threadIdx.x;
     const int col_in = lane & 15;
     const int row_hi = 4 * (lane >> 4);
-    const int cbase = HALF ? 128 * h : 0;
+    const int wrow = wm * 16 * MB;   // the wave's first tile row
     // No barrier here: in both kernels every wave's last operand read of the
     // stage buffers completes before a workgroup barrier that every wave has
     // passed before its last MFMAs (the ping-pong kernel: the end of group 1's
-    // last read turn; the half-tile kernel: the barrier before the last
-    // sub-step), so the buffers are free, and group 0 of the ping-pong kernel
-    // starts its epilogue while group 1 runs its last MFMA turn.
+    // last read turn; the short-tile kernel: the barrier before the last
+    // stage's MFMAs), so the buffers are free, and group 0 of the ping-pong
+    // kernel starts its epilogue while group 1 runs its last MFMA turn.
     if constexpr (EPI == EPI_SWIGLU) {
-        constexpr int OC = HALF ? 64 : 128;   // outputs per row of this workgroup
+        constexpr int OC = COLS / 2;   // outputs per row of this workgroup
         constexpr int LD = OC + 8;
         bf16_t* S = reinterpret_cast<bf16_t*>(stage);
-        const int sc = 64 * (wn >> 1) + 32 * (wn & 1) + col_in - (HALF ? 64 * h : 0);
+        const int sc = 64 * (wn >> 1) + 32 * (wn & 1) + col_in;
 #pragma unroll
-        for (int mb = 0; mb < 8; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const int r = wm * 128 + mb * 16 + row_hi + v;
+                    const int r = wrow + mb * 16 + row_hi + v;
                     const float gt = acc[mb][nb][v];
                     const float up = acc[mb][nb + 2][v];
                     // silu(g) = g / (1 + e^-g) with the hardware exp2 and reciprocal
@@ -226,8 +222,8 @@ __device__ __forceinline__ void epilogue_staged(const GemmParams& p, f32x4_t (&a
                 }
         __syncthreads();
         constexpr int VPR = OC / 8;
-        bf16_t* out = p.o0 + bn * 128 + (HALF ? 64 * h : 0);
-        for (int v = tid; v < 256 * VPR; v += NT) {
+        bf16_t* out = p.o0 + (n0 >> 1);
+        for (int v = tid; v < ROWS * VPR; v += NT) {
             const int r = v / VPR;
             const int cv = (v % VPR) * 8;
             const int row = m0 + r;
@@ -236,15 +232,15 @@ __device__ __forceinline__ void epilogue_staged(const GemmParams& p, f32x4_t (&a
                     *reinterpret_cast<const u32x4_t*>(S + r * LD + cv);
         }
     } else if constexpr (EPI == EPI_QKV) {
-        constexpr int OC = HALF ? 128 : 256;
+        constexpr int OC = COLS;
         constexpr int LD = OC + 8;
         bf16_t* S = reinterpret_cast<bf16_t*>(stage);
-        const int region = __builtin_amdgcn_readfirstlane((bn * BN) / p.d);
+        const int region = __builtin_amdgcn_readfirstlane(n0 / p.d);
         const int j = 32 * (wn & 1) + col_in;            // block nb = 0 column within the head (+16 for nb = 1)
-        const int sc = 128 * (wn >> 1) + j - cbase;      // staging column of j; j + 64 at sc + 64
+        const int sc = 128 * (wn >> 1) + j;              // staging column of j; j + 64 at sc + 64
         // Head dim 64: the rotate-half partner of column c (c mod 64 < 32) is
         // c + 32, held by the same lane and accumulator slot of wave wn ^ 1
-        // (wave index ^ 1, in whole and half tiles alike).  The two waves
+        // (wave index ^ 1, in 256- and 128-column tiles alike).  The two waves
         // swap their float32 values through LDS one row block at a time; each
         // keeps its own rotated half in acc, and the tile is then staged as v
         // is.  Angle index of (nb, lane): 16 (nb & 1) + col_in.
@@ -254,13 +250,13 @@ __device__ __forceinline__ void epilogue_staged(const GemmParams& p, f32x4_t (&a
             const int wave = threadIdx.x >> 6;
             const bool first = (wn & 1) == 0;             // holds j < 32 of its head
 #pragma unroll
-            for (int mb = 0; mb < 8; ++mb) {
+            for (int mb = 0; mb < MB; ++mb) {
 #pragma unroll
                 for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) X[(wave * 16 + nb * 4 + v) * 64 + lane] = acc[mb][nb][v];
                 __syncthreads();
-                const int r0 = wm * 128 + mb * 16 + row_hi;
+                const int r0 = wrow + mb * 16 + row_hi;
 #pragma unroll
                 for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
@@ -274,9 +270,9 @@ __device__ __forceinline__ void epilogue_staged(const GemmParams& p, f32x4_t (&a
             }
         }
 #pragma unroll
-        for (int mb = 0; mb < 8; ++mb) {
+        for (int mb = 0; mb < MB; ++mb) {
             __builtin_amdgcn_sched_barrier(0);
-            const int r0 = wm * 128 + mb * 16 + row_hi;
+            const int r0 = wrow + mb * 16 + row_hi;
             if (region == 2 || rope64) {
 #pragma unroll
                 for (int nb = 0; nb < 2; ++nb)
@@ -306,8 +302,8 @@ __device__ __forceinline__ void epilogue_staged(const GemmParams& p, f32x4_t (&a
         }
         __syncthreads();
         constexpr int VPR = OC / 8;
-        bf16_t* out = pick3(region, p.o0, p.o1, p.o2) + (bn * BN - region * p.d) + cbase;
-        for (int v = tid; v < 256 * VPR; v += NT) {
+        bf16_t* out = pick3(region, p.o0, p.o1, p.o2) + (n0 - region * p.d);
+        for (int v = tid; v < ROWS * VPR; v += NT) {
             const int r = v / VPR;
             const int cv = (v % VPR) * 8;
             const int row = m0 + r;
@@ -318,217 +314,270 @@ __device__ __forceinline__ void epilogue_staged(const GemmParams& p, f32x4_t (&a
     } else {   // RESID: x += A B^T in float32, read-modify-write straight from the lanes
         const int c0 = w8_c0(wn);
 #pragma unroll
-        for (int mp = 0; mp < 8; mp += 2) {   // two row blocks at a time
+        for (int mp = 0; mp < MB; mp += 2) {   // two row blocks at a time
             __builtin_amdgcn_sched_barrier(0);
             float old[2][4][4];
 #pragma unroll
             for (int e = 0; e < 2; ++e)
+                if (mp + e < MB)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int row = m0 + wm * 128 + (mp + e) * 16 + row_hi + v;
-                    const float* src = p.resid + (size_t)(row < p.M ? row : p.M - 1) * p.N + bn * BN + c0 + col_in;
+                    for (int v = 0; v < 4; ++v) {
+                        const int row = m0 + wrow + (mp + e) * 16 + row_hi + v;
+                        const float* src = p.resid + (size_t)(row < p.M ? row : p.M - 1) * p.N + n0 + c0 + col_in;
 #pragma unroll
-                    for (int nb = 0; nb < 4; ++nb) old[e][v][nb] = src[16 * (nb & 1) + 64 * (nb >> 1)];
-                }
+                        for (int nb = 0; nb < 4; ++nb) old[e][v][nb] = src[16 * (nb & 1) + 64 * (nb >> 1)];
+                    }
 #pragma unroll
             for (int e = 0; e < 2; ++e)
+                if (mp + e < MB)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int row = m0 + wm * 128 + (mp + e) * 16 + row_hi + v;
-                    if (row >= p.M) continue;
-                    float* dst = p.resid + (size_t)row * p.N + bn * BN + c0 + col_in;
+                    for (int v = 0; v < 4; ++v) {
+                        const int row = m0 + wrow + (mp + e) * 16 + row_hi + v;
+                        if (row >= p.M) continue;
+                        float* dst = p.resid + (size_t)row * p.N + n0 + c0 + col_in;
 #pragma unroll
-                    for (int nb = 0; nb < 4; ++nb)
-                        dst[16 * (nb & 1) + 64 * (nb >> 1)] = old[e][v][nb] + acc[mp + e][nb][v];
-                }
+                        for (int nb = 0; nb < 4; ++nb)
+                            dst[16 * (nb & 1) + 64 * (nb >> 1)] = old[e][v][nb] + acc[mp + e][nb][v];
+                    }
         }
         (void)stage;
-        (void)cbase;
     }
 }
 
-// Half-tile kernel: a workgroup of 4 waves computes one half (128 columns,
-// h = 0 or 1) of a 256x256 tile, as waves (wm, 2h + (wave & 1)) of the
-// whole-tile layout would; only those 128 B rows are loaded.  Used for the last
-// tiles of a GEMM so that the final round over the CUs is half as long.  Each
-// wave reads its operands for the next 32-deep sub-step while it runs the 32
-// MFMAs of the current one.  The barrier sits before sub-step 1: by then stage
-// kt+1 has landed and every wave has read the whole of stage kt, so sub-step 1
-// also issues the DMA of stage kt+2 into the buffer stage kt used, a stage
-// before it is needed.
-template <int EPI>
-__global__ void __launch_bounds__(256, 1) gemm_bf16_half_kernel(GemmParams p) {
-    __shared__ __align__(16) bf16_t lds[kStagingBytes / 2];   // two stages, then the epilogue tile
-    __shared__ int pos_lds[BM];   // QKV: clamped position of each tile row
-    int bm, bn, h;
-    {
-        const int i = xcd_remap(blockIdx.x, 2 * (p.num_m * p.num_n - p.n_full));
-        h = i & 1;
-        group_coords(p.n_full + (i >> 1), p.num_m, p.num_n, bm, bn);
-    }
-    const int m0 = bm * BM;
+// Short-tile kernel: tiles of 32 MB rows x 128 columns (MB = 1, 2, 4) on 4 waves
+// (2 x 2, each 16 MB x 64), one workgroup a CU.  It runs the GEMMs whose
+// 256-row tiles would leave most of the chip idle (few prompts, narrow
+// models) and the last tiles of the others.  What bounds it: a workgroup alone
+// on its CU has one wave a SIMD, so nothing hides the latency of its LDS reads
+// and DMA but its own schedule.  So the ring holds RING = 4 to 7 stages (RING - 1
+// in flight while one is computed; two stages exposed the DMA's full latency
+// in every stage), and each wave reads the whole next stage into registers while
+// it runs the MFMAs of the current one, with one barrier a stage.  What is left
+// is the LDS traffic, (64 + 64) rows read by each wave for 64 x 64 outputs.
+// Measured at M = 643 (one 576-token tile's prompt) on the output projection
+// (K = 4,096) and the down projection (K = 11,008), N = 4,096, weights in the
+// memory-side cache, MB = 4: 31 and 69 us; reading one 32-deep sub-step ahead
+// 41 and 100 us; 256 x 128 half tiles on a two-stage ring 75 and 194 us.  Two
+// workgroups a CU with rings half as deep were slower or equal wherever the
+// ping-pong tiles do not already win; 96-row tiles gained only with warm
+// weights.
+//
+// TAIL: the workgroups are the sub-tiles of the 256 x 256 tiles p.n_full ..;
+// otherwise the whole output in the grouped order.
+//
+// Stage kt sits in ring slot kt mod RING.  Before the MFMAs of stage kt every
+// wave waits for its reads of stage kt and for its DMA of stage kt + 1, and
+// passes a barrier: stage kt + 1 is then visible, slot kt mod RING is free, and
+// the DMA of stage kt + RING goes into it.
+template <int MB>
+constexpr int kShortRing = MB == 1 ? 7 : MB == 2 ? 6 : 4;   // the stages 160 KB of LDS hold
 
+template <int EPI, int MB, bool TAIL>
+__global__ void __launch_bounds__(256, 1) gemm_bf16_short_kernel(GemmParams p) {
+    constexpr int TM = 32 * MB;
+    constexpr int RING = kShortRing<MB>;
+    constexpr int kStage = (TM + 128) * BK3;   // elements: A rows, then B rows
+    __shared__ __align__(16) bf16_t lds[RING * kStage];
+    __shared__ int pos_lds[EPI == EPI_QKV ? TM : 1];   // QKV: clamped position of each tile row
+    int m0, n0;
+    if constexpr (TAIL) {
+        constexpr int SUB = 2 * (8 / MB);      // sub-tiles of a 256 x 256 tile
+        const int i = xcd_remap(blockIdx.x, SUB * (p.num_m * p.num_n - p.n_full));
+        int bm, bn;
+        group_coords(p.n_full + i / SUB, p.num_m, p.num_n, bm, bn);
+        m0 = bm * 256 + (i % SUB >> 1) * TM;
+        n0 = bn * 256 + (i & 1) * 128;
+        if (m0 >= p.M) return;
+    } else {
+        int bm, bn;
+        int t = round_remap(blockIdx.x, p.num_m * p.num_n);
+        if (p.reverse) t = p.num_m * p.num_n - 1 - t;
+        group_coords(t, p.num_m, p.num_n, bm, bn);
+        m0 = bm * TM;
+        n0 = bn * 128;
+    }
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1;
-    const int wn = 2 * h + (wave & 1);
+    const int wn = wave & 1;
 
-    // DMA: instructions 0..7 of this wave move A rows 8 (8 wave + j) +
-    // (lane >> 3), instructions 8..11 B rows 128 h + 8 (4 wave + j) +
-    // (lane >> 3).  Per-lane byte offsets are fixed for the whole K loop; the
-    // stage's K offset goes into the wave-uniform base.  LDS rows sit where
-    // the whole-tile kernel puts them.
-    constexpr int NA = 8;
-    constexpr int NB = 4;
-    constexpr int NQ = NA + NB;
-    uint32_t aoff[NA], boff[NB];
-    const bf16_t* bbase[NB];
-    int arow0[NA], brow0[NB];
+    // DMA: instructions 0 .. MB-1 of this wave move A rows 8 (MB wave + j) +
+    // (lane >> 3), the next four B rows 8 (4 wave + j) + (lane >> 3).
+    constexpr int NQ = MB + 4;
+    uint32_t aoff[MB], boff[4];
+    const bf16_t* bbase[4];
 #pragma unroll
-    for (int j = 0; j < NA; ++j) {
-        arow0[j] = 8 * (NA * wave + j);
-        const int row = arow0[j] + (lane >> 3);
+    for (int j = 0; j < MB; ++j) {
+        const int row = 8 * (MB * wave + j) + (lane >> 3);
         const int c = (lane & 7) ^ swz8(row);
-        int ar = m0 + row;
-        ar = ar < p.M ? ar : p.M - 1;
+        const int ar = m0 + row < p.M ? m0 + row : p.M - 1;
         aoff[j] = ((uint32_t)ar * (uint32_t)p.K + (uint32_t)c * 8u) * 2u;
     }
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        brow0[j] = 128 * h + 8 * (4 * wave + j);
-        const int row = brow0[j] + (lane >> 3);
+    for (int j = 0; j < 4; ++j) {
+        const int row = 8 * (4 * wave + j) + (lane >> 3);
         const int c = (lane & 7) ^ swz8(row);
-        boff[j] = ((uint32_t)b_row<EPI>(p, bn, row) * (uint32_t)p.K + (uint32_t)c * 8u) * 2u;
-        bbase[j] = b_base_row<EPI>(p, bn, brow0[j]);   // one matrix per 8-row group
+        boff[j] = ((uint32_t)b_row<EPI>(p, n0, row) * (uint32_t)p.K + (uint32_t)c * 8u) * 2u;
+        bbase[j] = b_base<EPI>(p, n0, 8 * (4 * wave + j));   // one matrix per 8-row group
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
-    auto dma_one = [&](int buf, int kt, int q) {   // q = 0..NQ-1: A chunks then B chunks
-        const uint32_t sb = lds0 + (uint32_t)buf * (kStage3 * 2);
+    auto dma_one = [&](int slot, int kt, int q) {
+        const uint32_t sb = lds0 + (uint32_t)slot * (kStage * 2);
         const size_t ko = (size_t)kt * BK3;
-        if (q < NA) dma16s(p.a + ko, aoff[q], sb + (uint32_t)arow0[q] * 128u);
-        else dma16s(bbase[q - NA] + ko, boff[q - NA], sb + BM * BK3 * 2 + (uint32_t)brow0[q - NA] * 128u);
+        if (q < MB) dma16s(p.a + ko, aoff[q], sb + (uint32_t)(MB * wave + q) * 1024u);
+        else dma16s(bbase[q - MB] + ko, boff[q - MB], sb + TM * 128u + (uint32_t)(4 * wave + q - MB) * 1024u);
     };
-
     if constexpr (EPI == EPI_QKV) {
-        for (int i = tid; i < BM; i += 256) {
-            int r = m0 + i;
-            r = r < p.M ? r : p.M - 1;
-            int ps = p.pos[r];
-            pos_lds[i] = ps < 0 ? 0 : (ps >= p.n_pos ? p.n_pos - 1 : ps);
+        if (tid < TM) {
+            const int r = m0 + tid < p.M ? m0 + tid : p.M - 1;
+            const int ps = p.pos[r];
+            pos_lds[tid] = ps < 0 ? 0 : (ps >= p.n_pos ? p.n_pos - 1 : ps);
         }
     }
 
-    f32x4_t acc[8][4];
+    f32x4_t acc[MB][4];
 #pragma unroll
-    for (int mb = 0; mb < 8; ++mb)
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < 4; ++nb) acc[mb][nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
     const int nk = p.K / BK3;
-    const int rd_a = (wm * 128 + (lane & 15)) * BK3;
-    const int rd_b = BM * BK3 + (w8_c0(wn) + (lane & 15)) * BK3;
+    const int rd_a = (wm * 16 * MB + (lane & 15)) * BK3;
+    const int rd_b = TM * BK3 + (w8_c0(wn) + (lane & 15)) * BK3;
     const int key = swz8(lane & 15);
     const int qsel = lane >> 4;
-    bf16x8_t fa[2][8], fb[2][4];
-    // LDS read q (0..11) of sub-step s of buffer buf, in the order the MFMAs
-    // consume them: a[0], b[0..3], a[1..7]
-    auto read_one = [&](int slot, int buf, int s, int q) {
-        const bf16_t* sA = lds + buf * kStage3;
+    constexpr int NR = MB + 4;               // operand reads of a 32-deep sub-step
+    constexpr int NM = 4 * MB;               // its MFMAs
+    bf16x8_t fa[2][2][MB], fb[2][2][4];      // [stage parity][sub-step][mb or nb]
+    // read r (0 .. 2 NR - 1) of a stage, in the order the MFMAs consume them:
+    // per sub-step a[0], b[0..3], a[1..]
+    auto read_one = [&](int par, int slot, int r) {
+        const bf16_t* sA = lds + slot * kStage;
+        const int s = r / NR, q = r % NR;
         const int sw = ((4 * s + qsel) ^ key) << 3;
         if (q == 0) {
-            fa[slot][0] = *reinterpret_cast<const bf16x8_t*>(sA + rd_a + sw);
+            fa[par][s][0] = *reinterpret_cast<const bf16x8_t*>(sA + rd_a + sw);
         } else if (q <= 4) {
             const int nb = q - 1;
-            fb[slot][nb] = *reinterpret_cast<const bf16x8_t*>(sA + rd_b + sw + (16 * (nb & 1) + 64 * (nb >> 1)) * BK3);
+            fb[par][s][nb] =
+                *reinterpret_cast<const bf16x8_t*>(sA + rd_b + sw + (16 * (nb & 1) + 64 * (nb >> 1)) * BK3);
         } else {
-            fa[slot][q - 4] = *reinterpret_cast<const bf16x8_t*>(sA + rd_a + sw + (q - 4) * 16 * BK3);
+            fa[par][s][q - 4] = *reinterpret_cast<const bf16x8_t*>(sA + rd_a + sw + (q - 4) * 16 * BK3);
         }
     };
-    auto mfma_one = [&](int slot, int i) {   // i = 0..31: (mb, nb) = (i >> 2, snake(i))
-        const int mb = i >> 2, nb = snake_nb(i);
-        acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[slot][mb], fb[slot][nb], acc[mb][nb], 0, 0, 0);
+    auto mfma_one = [&](int par, int i) {    // i = 0 .. 2 NM - 1
+        const int s = i / NM, mb = (i % NM) >> 2, nb = snake_nb(i % NM);
+        acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[par][s][mb], fb[par][s][nb], acc[mb][nb], 0, 0, 0);
     };
 
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) dma_one(0, 0, q);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    for (int j = 0; j < RING; ++j)
+        if (j < nk) {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) dma_one(j, j, q);
+        }
+    if (nk >= RING) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((RING - 1) * NQ) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     wg_barrier();
-    if (nk > 1) {
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) dma_one(1, 1, q);
-    }
-#pragma unroll
-    for (int q = 0; q < 12; ++q) read_one(0, 0, 0, q);
+    for (int r = 0; r < 2 * NR; ++r) read_one(0, 0, r);
 
-    // sub-step 0 reads sub-step 1 of the stage; sub-step 1 issues the DMA of
-    // stage kt + 2 and reads sub-step 0 of stage kt + 1
-    auto stage = [&](int kt, auto kDma, auto kMore) {
-        const int cur = kt & 1;
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < 32; ++i) {
-            mfma_one(0, i);
-            if ((i & 1) == 0 && (i >> 1) < 12) read_one(1, cur, 1, i >> 1);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    int cur = 0;   // kt mod RING
+    // kPar: kt mod 2; kDma: issue stage kt + RING; kMore: a stage kt + 1 follows;
+    // kWait: this wave's DMA instructions that may still be in flight once stage
+    // kt + 1 has landed
+    auto stage = [&](int kt, auto kPar, auto kDma, auto kMore, auto kWait) {
+        constexpr int P = decltype(kPar)::value;
+        const int nxt = cur + 1 == RING ? 0 : cur + 1;
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(decltype(kWait)::value) : "memory");
         wg_barrier();
 #pragma unroll
-        for (int m = 0; m < 8; ++m) asm volatile("" : "+v"(fa[1][m]));
+        for (int s = 0; s < 2; ++s) {
 #pragma unroll
-        for (int n = 0; n < 4; ++n) asm volatile("" : "+v"(fb[1][n]));
+            for (int m = 0; m < MB; ++m) asm volatile("" : "+v"(fa[P][s][m]));
+#pragma unroll
+            for (int n = 0; n < 4; ++n) asm volatile("" : "+v"(fb[P][s][n]));
+        }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < 32; ++i) {
-            mfma_one(1, i);
-            if constexpr (decltype(kDma)::value) {
-                if ((i & 1) == 1 && (i >> 1) < NQ) dma_one(cur, kt + 2, i >> 1);
-            }
+        for (int i = 0; i < 2 * NM; ++i) {
+            mfma_one(P, i);
             if constexpr (decltype(kMore)::value) {
-                if ((i & 1) == 0 && (i >> 1) < 12) read_one(0, cur ^ 1, 0, i >> 1);
+                if (i < 2 * NR) read_one(1 - P, nxt, i);
+                if (i == 2 * NM - 1) {   // MB = 1: more reads than MFMAs
+#pragma unroll
+                    for (int r = 2 * NM; r < 2 * NR; ++r) read_one(1 - P, nxt, r);
+                }
+            }
+            if constexpr (decltype(kDma)::value) {
+#pragma unroll
+                for (int q = (i * NQ) / (2 * NM); q < ((i + 1) * NQ) / (2 * NM); ++q) dma_one(cur, kt + RING, q);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
+        cur = nxt;
     };
     using T_ = std::true_type;
     using F_ = std::false_type;
+    using P0 = std::integral_constant<int, 0>;
+    using P1 = std::integral_constant<int, 1>;
+    using W = std::integral_constant<int, (RING - 2) * NQ>;   // stages kt + 2 .. kt + RING - 1
+    using W0 = std::integral_constant<int, 0>;
     int kt = 0;
-    for (; kt + 2 < nk; ++kt) stage(kt, T_{}, T_{});
-    if (kt + 1 < nk) stage(kt++, F_{}, T_{});
-    stage(kt, F_{}, F_{});
-    epilogue_staged<EPI, true>(p, acc, m0, bn, h, wm, wn, lane, pos_lds, reinterpret_cast<unsigned char*>(lds));
+    for (; kt + 1 + RING < nk; kt += 2) {
+        stage(kt, P0{}, T_{}, T_{}, W{});
+        stage(kt + 1, P1{}, T_{}, T_{}, W{});
+    }
+    for (; kt < nk; kt += 2) {   // the last RING stages, and the one before them when that is even
+        if (kt + RING < nk) stage(kt, P0{}, T_{}, T_{}, W{});
+        else if (kt + 1 < nk) stage(kt, P0{}, F_{}, T_{}, W0{});
+        else stage(kt, P0{}, F_{}, F_{}, W0{});
+        if (kt + 1 >= nk) break;
+        if (kt + 2 < nk) stage(kt + 1, P1{}, F_{}, T_{}, W0{});
+        else stage(kt + 1, P1{}, F_{}, F_{}, W0{});
+    }
+    epilogue_staged<EPI, MB, 128>(p, acc, m0, n0, wm, wn, lane, pos_lds, reinterpret_cast<unsigned char*>(lds));
 }
 
 // ---------------------------------------------------------------------------
-// Ping-pong kernel (every whole tile).  The 2 x 4 wave layout above, with the
-// same LDS stages and order of accumulation as the half-tile kernel; the two
-// waves that share a SIMD take turns: while one issues the 64 MFMAs of a whole 64-deep stage from
-// registers, the other reads its operands for the next stage from LDS, and a
-// workgroup barrier separates the turns.  Waves 0-3 (rows 0-127 of the tile)
-// run one turn ahead of waves 4-7 (rows 128-255); the hardware places waves w
-// and w + 4 of a 512-thread workgroup on the same SIMD, so every SIMD holds one
-// wave of each group and its MFMA pipe is fed by one of them at every moment.
+// Ping-pong kernel: tiles of 32 MB rows (MB = 5..8) x 256 columns.  The 2 x 4
+// wave layout above, with the same LDS stages and order of accumulation as the
+// short-tile kernel; the two waves that share a SIMD take turns: while one
+// issues the 8 MB MFMAs of a whole 64-deep stage from registers, the other
+// reads its operands for the next stage from LDS, and a workgroup barrier
+// separates the turns.  Waves 0-3 (the tile's upper half) run one turn ahead of
+// waves 4-7 (the lower half); the hardware places waves w and w + 4 of a
+// 512-thread workgroup on the same SIMD, so every SIMD holds one wave of each
+// group and its MFMA pipe is fed by one of them at every moment.
 //
 // Turn t (each ends with a barrier of all eight waves):
 //   group 0: t = 2j   reads stage j          t = 2j+1  MFMAs of stage j
 //   group 1: t = 2j+1 reads stage j          t = 2j+2  MFMAs of stage j
 // Stage j sits in buffer j mod 2 and is last read in turn 2j+1, so the LDS
 // DMA of stage j+2 is issued in turn 2j+2, all of it by group 0 while it reads
-// stage j+1 (wave w moves its own rows and those of wave w + 4): the MFMA turns
-// issue nothing but MFMAs, and the read turns have time to spare.  Group 0
-// waits for that DMA at the end of turn 2j+3, before it reads stage j+2.
-template <int EPI>
+// stage j+1: the MFMA turns issue nothing but MFMAs, and the read turns have
+// time to spare.  Group 0 waits for that DMA at the end of turn 2j+3, before it
+// reads stage j+2.
+//
+// Shorter tiles (MB < 8) move more LDS bytes per flop, so a stage of 160 rows
+// still takes about 3/4 of the time of one of 256; they run where they save
+// more than that in rounds over the CUs.
+template <int EPI, int MB>
 __global__ void __launch_bounds__(512, 1) gemm_bf16_pp_kernel(GemmParams p) {
-    __shared__ __align__(16) bf16_t lds[kStagingBytes / 2];   // two stages, then the epilogue tile
-    __shared__ int pos_lds[BM];   // QKV: clamped position of each tile row
+    constexpr int TM = 32 * MB;
+    constexpr int kStage = (TM + BN) * BK3;                 // elements: A rows, then B rows
+    constexpr int kTile = TM * (BN + 8);                    // the largest epilogue tile (QKV), elements
+    __shared__ __align__(16) bf16_t lds[2 * kStage > kTile ? 2 * kStage : kTile];
+    __shared__ int pos_lds[TM];   // QKV: clamped position of each tile row
     int bm, bn;
     {
         int t = round_remap(blockIdx.x, p.n_full);
         if (p.reverse) t = p.n_full - 1 - t;
         group_coords(t, p.num_m, p.num_n, bm, bn);
     }
-    const int m0 = bm * BM;
+    const int m0 = bm * TM;
+    const int n0 = bn * BN;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -536,78 +585,71 @@ __global__ void __launch_bounds__(512, 1) gemm_bf16_pp_kernel(GemmParams p) {
     const int wm = wave >> 2;   // also the group
     const int wn = wave & 3;
 
-    // DMA: instruction j (0..3) of a wave moves A-tile rows and B-tile rows
-    // 8 (4 wave + j) + (lane >> 3) of the stage.
-    uint32_t aoff[4], boff[4];
-    const bf16_t* bbase[4];
+    // DMA of a stage by the four waves of a group: wave wn moves A rows 8 (MB
+    // wn + q), q < MB, and B rows 8 (8 wn + q), q < 8, plus lane / 8 each.  The
+    // 64 B rows of a wave are consecutive rows of one matrix (for SWIGLU 64
+    // gate or 64 up rows), so the q-th B source is a scalar step from the
+    // first; the swizzle differs between even and odd q only.  A rows past M
+    // repeat the last one, so their offsets are formed at each use.
+    const int brow = b_row<EPI>(p, n0, 64 * wn);
+    const bf16_t* bsrc = b_base<EPI>(p, n0, 64 * wn) + (size_t)brow * p.K;
+    const int lrow = lane >> 3;
+    uint32_t boff[2];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int row = 8 * (4 * wave + j) + (lane >> 3);
-        const int c = (lane & 7) ^ swz8(row);
-        int ar = m0 + row;
-        ar = ar < p.M ? ar : p.M - 1;
-        aoff[j] = ((uint32_t)ar * (uint32_t)p.K + (uint32_t)c * 8u) * 2u;
-        boff[j] = ((uint32_t)b_row<EPI>(p, bn, row) * (uint32_t)p.K + (uint32_t)c * 8u) * 2u;
-        bbase[j] = b_base_row<EPI>(p, bn, 8 * (4 * wave + j));
-    }
-    const uint32_t ring_wave = (uint32_t)(uintptr_t)lds + (uint32_t)wave * 4096u;
-    auto dma_one = [&](int kt, int q) {   // q = 0..7: A chunks 0..3 then B chunks 0..3
-        const uint32_t sb = ring_wave + (uint32_t)(kt & 1) * (kStage3 * 2);
+    for (int e = 0; e < 2; ++e)
+        boff[e] = ((uint32_t)lrow * (uint32_t)p.K + (uint32_t)((lane & 7) ^ swz8(8 * e + lrow)) * 8u) * 2u;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+    constexpr int ND = MB + 8;
+    auto dma_one = [&](int kt, int q) {
+        const uint32_t sb = lds0 + (uint32_t)(kt & 1) * (kStage * 2);
         const size_t ko = (size_t)kt * BK3;
-        if (q < 4) dma16s(p.a + ko, aoff[q], sb + q * 1024u);
-        else dma16s(bbase[q - 4] + ko, boff[q - 4], sb + BM * BK3 * 2 + (q - 4) * 1024u);
-    };
-    // the share of wave w + 4 (rows + 128), issued by wave w of group 0; the B
-    // row of tile row r + 128 is that of r plus 128 (64 for SWIGLU), same matrix
-    const uint32_t bdelta = (uint32_t)(EPI == EPI_SWIGLU ? 64 : 128) * (uint32_t)p.K * 2u;
-    auto dma_partner = [&](int kt, int q) {
-        const uint32_t sb = ring_wave + 4u * 4096u + (uint32_t)(kt & 1) * (kStage3 * 2);
-        const size_t ko = (size_t)kt * BK3;
-        if (q < 4) {
-            const int row = 8 * (4 * (wave + 4) + q) + (lane >> 3);
+        if (q < MB) {
+            const int row = 8 * (MB * wn + q) + lrow;
             const int c = (lane & 7) ^ swz8(row);
-            int ar = m0 + row;
-            ar = ar < p.M ? ar : p.M - 1;
-            dma16s(p.a + ko, ((uint32_t)ar * (uint32_t)p.K + (uint32_t)c * 8u) * 2u, sb + q * 1024u);
+            const int ar = m0 + row < p.M ? m0 + row : p.M - 1;
+            dma16s(p.a + ko, ((uint32_t)ar * (uint32_t)p.K + (uint32_t)c * 8u) * 2u,
+                   sb + (uint32_t)(MB * wn + q) * 1024u);
         } else {
-            dma16s(bbase[q - 4] + ko, boff[q - 4] + bdelta, sb + BM * BK3 * 2 + (q - 4) * 1024u);
+            const int j = q - MB;
+            dma16s(bsrc + ko + (size_t)(8 * j) * p.K, boff[j & 1], sb + TM * 128u + (uint32_t)(8 * wn + j) * 1024u);
         }
     };
 
     if constexpr (EPI == EPI_QKV) {
-        if (tid < BM) {
-            int r = m0 + tid;
-            r = r < p.M ? r : p.M - 1;
-            int ps = p.pos[r];
+        if (tid < TM) {
+            const int r = m0 + tid < p.M ? m0 + tid : p.M - 1;
+            const int ps = p.pos[r];
             pos_lds[tid] = ps < 0 ? 0 : (ps >= p.n_pos ? p.n_pos - 1 : ps);
         }
     }
 
-    f32x4_t acc[8][4];
+    f32x4_t acc[MB][4];
 #pragma unroll
-    for (int mb = 0; mb < 8; ++mb)
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < 4; ++nb) acc[mb][nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
     const int nk = p.K / BK3;
-    const int rd_a = (wm * 128 + (lane & 15)) * BK3;
-    const int rd_b = BM * BK3 + (w8_c0(wn) + (lane & 15)) * BK3;
+    const int rd_a = (wm * 16 * MB + (lane & 15)) * BK3;
+    const int rd_b = TM * BK3 + (w8_c0(wn) + (lane & 15)) * BK3;
     const int key = swz8(lane & 15);
     const int qsel = lane >> 4;
-    bf16x8_t fa[2][8], fb[2][4];   // [32-deep sub-step][mb or nb]: one whole stage
-    auto read_one = [&](int kt, int r) {   // r = 0..23: sub-step r / 12, operand r % 12
-        const bf16_t* sA = lds + (kt & 1) * kStage3;
-        const int s = r / 12, q = r % 12;
+    constexpr int NR = MB + 4;
+    bf16x8_t fa[2][MB], fb[2][4];   // [32-deep sub-step][mb or nb]: one whole stage
+    auto read_one = [&](int kt, int r) {   // r = 0 .. 2 NR - 1: sub-step r / NR, operand r % NR
+        const bf16_t* sA = lds + (kt & 1) * kStage;
+        const int s = r / NR, q = r % NR;
         const int sw = ((4 * s + qsel) ^ key) << 3;
-        if (q < 8) {
+        if (q < MB) {
             fa[s][q] = *reinterpret_cast<const bf16x8_t*>(sA + rd_a + sw + q * 16 * BK3);
         } else {
-            const int nb = q - 8;
+            const int nb = q - MB;
             fb[s][nb] = *reinterpret_cast<const bf16x8_t*>(sA + rd_b + sw + (16 * (nb & 1) + 64 * (nb >> 1)) * BK3);
         }
     };
-    auto mfma_one = [&](int i) {   // i = 0..63: sub-step i / 32, (mb, nb) = ((i >> 2) & 7, snake(i))
-        const int s = i >> 5, mb = (i >> 2) & 7, nb = snake_nb(i);
+    constexpr int NM = 4 * MB;
+    auto mfma_one = [&](int i) {   // i = 0 .. 2 NM - 1: sub-step i / NM, (mb, nb) = (i >> 2, snake(i))
+        const int s = i / NM, mb = (i % NM) >> 2, nb = snake_nb(i % NM);
         acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[s][mb], fb[s][nb], acc[mb][nb], 0, 0, 0);
     };
     auto turn_end = [&]() {
@@ -615,15 +657,14 @@ __global__ void __launch_bounds__(512, 1) gemm_bf16_pp_kernel(GemmParams p) {
         wg_barrier();
         __builtin_amdgcn_sched_barrier(0);
     };
-    // reads of stage kt; with kDma (group 0 only), the DMA of stage kt + 1 for
-    // this wave's rows and for those of wave + 4
+    // reads of stage kt; with kDma (group 0 only), the DMA of stage kt + 1
     auto read_turn = [&](int kt, auto kDma) {
 #pragma unroll
-        for (int r = 0; r < 24; ++r) {
+        for (int r = 0; r < 2 * NR; ++r) {
             read_one(kt, r);
             if constexpr (decltype(kDma)::value) {
-                if (r % 3 == 2) dma_one(kt + 1, r / 3);
-                if (r % 3 == 0) dma_partner(kt + 1, r / 3);
+#pragma unroll
+                for (int q = (r * ND) / (2 * NR); q < ((r + 1) * ND) / (2 * NR); ++q) dma_one(kt + 1, q);
             }
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -632,7 +673,7 @@ __global__ void __launch_bounds__(512, 1) gemm_bf16_pp_kernel(GemmParams p) {
     auto mfma_turn = [&]() {
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-        for (int i = 0; i < 64; ++i) {
+        for (int i = 0; i < 2 * NM; ++i) {
             mfma_one(i);
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -641,15 +682,14 @@ __global__ void __launch_bounds__(512, 1) gemm_bf16_pp_kernel(GemmParams p) {
     using T_ = std::true_type;
     using F_ = std::false_type;
 
-    // prologue: stages 0 and 1 in flight, wait for stage 0
+    // prologue: group 0 issues and awaits stage 0, group 1 issues stage 1
+    if (wm == 0) {
 #pragma unroll
-    for (int q = 0; q < 8; ++q) dma_one(0, q);
-    if (nk > 1) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) dma_one(1, q);
-        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-    } else {
+        for (int q = 0; q < ND; ++q) dma_one(0, q);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    } else if (nk > 1) {
+#pragma unroll
+        for (int q = 0; q < ND; ++q) dma_one(1, q);
     }
     turn_end();
 
@@ -677,7 +717,7 @@ __global__ void __launch_bounds__(512, 1) gemm_bf16_pp_kernel(GemmParams p) {
             if (kt + 1 < nk) turn_end();
         }
     }
-    epilogue_staged<EPI, false>(p, acc, m0, bn, 0, wm, wn, lane, pos_lds, reinterpret_cast<unsigned char*>(lds));
+    epilogue_staged<EPI, MB, BN>(p, acc, m0, n0, wm, wn, lane, pos_lds, reinterpret_cast<unsigned char*>(lds));
 }
 
 int cu_count() {
@@ -692,27 +732,112 @@ int cu_count() {
     return cache[dev];
 }
 
-// Whole 256x256 tiles first (ping-pong kernel), then, if the tiles of the last
-// round over the CUs fill at most half of it, those tiles as two 256x128
-// halves each (half-tile kernel), so that round takes about half as long.
-// Every output element is accumulated in the same order by both kernels.
+// How a GEMM runs: ping-pong tiles of 32 pp rows (0: none), then `tail` sub-tile
+// rows / 32 for the 256-row tiles of the last round (0: none), or short tiles
+// of 32 shrt rows for everything.
+struct GemmPlan {
+    int pp, tail, shrt;
+};
+
+// Time of one 64-deep stage of a tile with the chip busy and weights cold (ns),
+// what a tile costs besides its stages (first DMA, epilogue) and what the
+// second launch of a tail costs besides its tiles.  From sweeps of every plan
+// over M = 176 .. 18,739 and widths 512 .. 4,096; the pick was within 5% of the
+// fastest plan in all of them.  At d = 4,096, FFN 11,008 (us; the first figure
+// the 256-row tiles alone): M = 643 QKV 93 -> 89 (160-row tiles), out 82 -> 33
+// and down 221 -> 76 (128-row short tiles), gate/up 155 -> 113 (two of 258 tiles
+// as a tail); M = 3,075 (16 prompts) 283 -> 257, 94 -> 90, 450 -> 414 and
+// 247 -> 236, all as 224-row tiles; M = 18,739 keeps the 256-row tiles.
+constexpr float kPpStage[9] = {0, 0, 0, 0, 0, 1080, 1180, 1320, 1440};
+constexpr float kShortStage[5] = {0, 300, 360, 0, 470};
+constexpr float kTileFixed = 5000;
+constexpr float kTailFixed = 10000;
+
+// The cheapest plan by rounds over the CUs times the cost of a round.  Every
+// output element is accumulated in the same order by every plan, so the
+// choice changes no result.
+GemmPlan plan_gemm(int M, int num_n, int K, int cus) {
+    const float nk = (float)(K / BK3);
+    auto rounds = [&](long long tiles) { return (float)((tiles + cus - 1) / cus); };
+    GemmPlan best{8, 0, 0};
+    float cost = 0;
+    for (int mb = 8; mb >= 5; --mb) {
+        const long long nt = (long long)((M + 32 * mb - 1) / (32 * mb)) * num_n;
+        const float c = rounds(nt) * (nk * kPpStage[mb] + kTileFixed);
+        if (mb == 8 || c < cost) {
+            best = GemmPlan{mb, 0, 0};
+            cost = c;
+        }
+    }
+    const long long nt = (long long)((M + 255) / 256) * num_n, rem = nt % cus;
+    if (nt >= cus && rem != 0)
+        for (int mb = 4; mb >= 1; mb /= 2) {
+            const float c = (float)(nt / cus) * (nk * kPpStage[8] + kTileFixed) +
+                            rounds(rem * 2 * (8 / mb)) * (nk * kShortStage[mb] + kTileFixed) + kTailFixed;
+            if (c < cost) {
+                best = GemmPlan{8, mb, 0};
+                cost = c;
+            }
+        }
+    for (int mb = 4; mb >= 1; mb /= 2) {
+        const long long ns = (long long)((M + 32 * mb - 1) / (32 * mb)) * num_n * 2;
+        const float c = rounds(ns) * (nk * kShortStage[mb] + kTileFixed);
+        if (c < cost) {
+            best = GemmPlan{0, 0, mb};
+            cost = c;
+        }
+    }
+    return best;
+}
+
+template <int EPI, int MB>
+hipError_t launch_pp(GemmParams p, hipStream_t st) {
+    hipLaunchKernelGGL((gemm_bf16_pp_kernel<EPI, MB>), dim3(p.n_full), dim3(512), 0, st, p);
+    return hipGetLastError();
+}
+
+template <int EPI, int MB, bool TAIL>
+hipError_t launch_short(const GemmParams& p, hipStream_t st) {
+    const int tiles = TAIL ? 2 * (8 / MB) * (p.num_m * p.num_n - p.n_full) : p.num_m * p.num_n;
+    hipLaunchKernelGGL((gemm_bf16_short_kernel<EPI, MB, TAIL>), dim3(tiles), dim3(256), 0, st, p);
+    return hipGetLastError();
+}
+
 template <int EPI>
-hipError_t launch_gemm(GemmParams p, int num_n, hipStream_t st) {
-    if (p.M <= 0) return hipSuccess;
-    p.num_m = (p.M + BM - 1) / BM;
+hipError_t run_plan(GemmParams p, int num_n, const GemmPlan& plan, int cus, hipStream_t st) {
+    if (plan.shrt > 0) {
+        p.num_m = (p.M + 32 * plan.shrt - 1) / (32 * plan.shrt);
+        p.num_n = 2 * num_n;
+        switch (plan.shrt) {
+            case 1: return launch_short<EPI, 1, false>(p, st);
+            case 2: return launch_short<EPI, 2, false>(p, st);
+            default: return launch_short<EPI, 4, false>(p, st);
+        }
+    }
+    p.num_m = (p.M + 32 * plan.pp - 1) / (32 * plan.pp);
     p.num_n = num_n;
     const int nt = p.num_m * num_n;
-    const int cus = cu_count();
-    const int rem = nt % cus;
-    p.n_full = (2 * rem <= cus) ? nt - rem : nt;
-    if (p.n_full > 0) {
-        hipLaunchKernelGGL(gemm_bf16_pp_kernel<EPI>, dim3(p.n_full), dim3(512), 0, st, p);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+    p.n_full = plan.tail > 0 ? nt - nt % cus : nt;
+    hipError_t e = hipSuccess;
+    switch (plan.pp) {
+        case 5: e = launch_pp<EPI, 5>(p, st); break;
+        case 6: e = launch_pp<EPI, 6>(p, st); break;
+        case 7: e = launch_pp<EPI, 7>(p, st); break;
+        default: e = launch_pp<EPI, 8>(p, st); break;
     }
-    if (nt > p.n_full)
-        hipLaunchKernelGGL(gemm_bf16_half_kernel<EPI>, dim3(2 * (nt - p.n_full)), dim3(256), 0, st, p);
-    return hipGetLastError();
+    if (e != hipSuccess || nt == p.n_full) return e;
+    switch (plan.tail) {
+        case 1: return launch_short<EPI, 1, true>(p, st);
+        case 2: return launch_short<EPI, 2, true>(p, st);
+        default: return launch_short<EPI, 4, true>(p, st);
+    }
+}
+
+template <int EPI>
+hipError_t launch_gemm(const GemmParams& p, int num_n, hipStream_t st) {
+    if (p.M <= 0) return hipSuccess;
+    const int cus = cu_count();
+    return run_plan<EPI>(p, num_n, plan_gemm(p.M, num_n, p.K, cus), cus, st);
 }
 
 }  // namespace
