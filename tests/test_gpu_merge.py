@@ -201,3 +201,46 @@ def test_scene_query_with_merge_and_shared_prefix(R):
         a0, a1 = int(cua[i]), int(cua[i + 1])
         assert np.array_equal(ha[a0:a0 + n_sys], hb[:n_sys]), i
         assert np.array_equal(ha[a0 + n_sys:a1], hb[int(cub[i + 1]):int(cub[i + 2])]), i
+
+
+@pytest.mark.parametrize("d,n_v,kd,kcs,how", [
+    (32, 40, 5, (2, 16, 17), "plain"), (96, 70, 0, (3, 33, 64), "near"), (416, 300, 40, (65, 130, 12), "near"),
+    (4096, 200, 20, (10, 45, 90), "near"), (1056, 120, 8, (7, 48, 20), "scales"), (288, 90, 4, (6, 31, 65), "inf")])
+def test_merge_bf16_scores_decide_as_float64(R, d, n_v, kd, kcs, how):
+    """The bfloat16 assignment (float32 MFMA scores, cdot where they leave more
+    than one candidate) against the float32-storage path, which evaluates cdot
+    for every target, on the same values: the same groups, so the same rows
+    once rounded to bfloat16.  `near`: tokens in tight clusters, whose best
+    targets differ by less than the scores' error, and equal ones; `scales`:
+    tokens from 2^-70 to 2^90, zero rows among them (the bound's range and
+    outside it); `inf`: infinities in two tokens.  Finite cases also against the
+    oracle."""
+    rng = np.random.default_rng(d + n_v)
+    n_tiles = len(kcs)
+    x = rng.standard_normal((n_tiles, n_v, d)).astype(np.float32)
+    if how == "near":
+        base = rng.standard_normal((n_tiles, 3, d)).astype(np.float32)
+        x = base[:, rng.integers(0, 3, n_v)] + np.float32(2e-3) * x
+        x[:, 11] = x[:, 3]
+    if how == "scales":
+        x *= np.exp2(rng.integers(-70, 90, (n_tiles, n_v, 1))).astype(np.float32)
+        x[:, ::13] = 0
+        x[0] *= np.float32(2.0 ** -40) * (np.abs(x[0]) < 2.0 ** 60)
+    if how == "inf":
+        x[1, 17, 5] = np.inf
+        x[2, 0, 3] = -np.inf
+    b = synth.store(x, "bf16")
+    f = synth.bf16_to_f32(b) if hasattr(synth, "bf16_to_f32") else (b.astype(np.uint32) << 16).view(np.float32)
+    kept = list(range(n_tiles))[::-1]
+    dom = [np.sort(rng.choice(np.arange(1, n_v), kd, replace=False)) for _ in kept]
+    offs = (np.arange(n_tiles + 1) * kd).astype(np.int32)
+    sel = np.concatenate(dom).astype(np.int32)
+    got, coffs, st = run_merge(R, b, "bf16", kept, offs, sel, kcs)
+    ref, _, st2 = run_merge(R, f, "f32", kept, offs, sel, kcs)
+    assert st == 0 and st2 == 0
+    fin = np.isfinite(ref)
+    with np.errstate(invalid="ignore"):
+        assert np.array_equal(got[fin], O.round_f32_to_bf16(ref[fin]))
+    assert np.array_equal(np.isfinite((got.astype(np.uint32) << 16).view(np.float32)), fin)
+    if how != "inf":
+        assert np.array_equal(got, oracle_ctx(b, "bf16", kept, offs, sel, kcs))
