@@ -37,8 +37,6 @@
 // queries sit at logical positions n_prefix onwards.  Key blocks still start
 // at logical key 0, so the result is the same, bit for bit, as with the prefix
 // packed into every sequence.
-//
-// The float32 path (small models) is a plain per-query loop.
 #include "launch.h"
 #include "rift_common.h"
 
@@ -436,45 +434,6 @@ attn_worklist_kernel(const int* __restrict__ cu, int n_seq, int hs, int2* __rest
     for (int i = carry + tid; i < n_list; i += 1024) list[i] = int2{-1, 0};
 }
 
-template <int D>
-__global__ void __launch_bounds__(128)
-attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
-                const float* __restrict__ v, float* __restrict__ o, const int* __restrict__ cu,
-                int n_seq, int H, int n_prefix, float scale) {
-    const int seq = blockIdx.x % n_seq;
-    const int head = blockIdx.x / n_seq;
-    const int s0 = cu[seq];
-    const int L = cu[seq + 1] - s0;
-    const int pre = seq > 0 ? n_prefix : 0;   // shared prefix rows [0, pre) come first
-    const int ld = H * D;
-    for (int i = threadIdx.x; i < L; i += blockDim.x) {
-        const float* qi = q + (size_t)(s0 + i) * ld + head * D;
-        float acc[D];
-#pragma unroll
-        for (int c = 0; c < D; ++c) acc[c] = 0.f;
-        float m = -INFINITY, l = 0.f;
-        for (int jl = 0; jl <= pre + i; ++jl) {
-            const size_t row = jl < pre ? (size_t)jl : (size_t)(s0 + jl - pre);
-            const float* kj = k + row * ld + head * D;
-            float s = 0.f;
-#pragma unroll
-            for (int c = 0; c < D; ++c) s = fmaf(qi[c], kj[c], s);
-            s *= scale;
-            const float mn = fmaxf(m, s);
-            const float a = expf(m - mn);
-            const float p = expf(s - mn);
-            l = l * a + p;
-            const float* vj = v + row * ld + head * D;
-#pragma unroll
-            for (int c = 0; c < D; ++c) acc[c] = acc[c] * a + p * vj[c];
-            m = mn;
-        }
-        float* oi = o + (size_t)(s0 + i) * ld + head * D;
-#pragma unroll
-        for (int c = 0; c < D; ++c) oi[c] = acc[c] / l;
-    }
-}
-
 }  // namespace
 
 int attention_worklist_entries(int T, int n_seq, int n_heads) {
@@ -515,21 +474,6 @@ hipError_t launch_attention_bf16(const uint16_t* q, const uint16_t* k, const uin
     else
         hipLaunchKernelGGL((attn_bf16_kernel<4, 2, 64, false>), dim3((unsigned)blocks), dim3(256), 0, st, q, k, v,
                            o, cu, n_seq, n_heads, n_prefix, scale_log2, nullptr);
-    return hipGetLastError();
-}
-
-hipError_t launch_attention_f32(const float* q, const float* k, const float* v, float* o,
-                                const int* cu, int n_seq, int max_seqlen, int n_heads, int hd,
-                                int n_prefix, hipStream_t st) {
-    if (n_seq <= 0 || max_seqlen <= 0) return hipSuccess;
-    const float scale = 1.0f / sqrtf((float)hd);
-    const dim3 grid((unsigned)(n_seq * n_heads));
-    if (hd == 64)
-        hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(128), 0, st, q, k, v, o, cu, n_seq,
-                           n_heads, n_prefix, scale);
-    else
-        hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(128), 0, st, q, k, v, o, cu, n_seq,
-                           n_heads, n_prefix, scale);
     return hipGetLastError();
 }
 

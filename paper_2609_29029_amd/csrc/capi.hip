@@ -100,7 +100,7 @@ rift_status debug_scan(const DebugInput* in, int count, int* flag, hipStream_t s
 inline int dt_kind(rift_dtype dt) { return dt == RIFT_BF16 ? 0 : 1; }
 
 struct PrefillLayout {
-    size_t rope, h, q, k, v, a, gate2, alist, dbg, total;
+    size_t rope, h, q, k, v, a, alist, dbg, total;
 };
 
 // Entries of the query-block attention's work list the workspace holds (any
@@ -126,8 +126,6 @@ PrefillLayout prefill_layout(const rift_model_cfg& c, int64_t T, int64_t P) {
     off += align_up((size_t)T * c.d * e);
     L.a = off;
     off += align_up((size_t)T * c.ffn * e);
-    L.gate2 = off;
-    if (c.dt == RIFT_F32) off += align_up((size_t)T * c.ffn * e);
     L.alist = off;
     off += align_up((size_t)attention_list_capacity(c, T) * sizeof(int2));
     L.dbg = off;   // debug mode: flag word of the input scan
@@ -678,29 +676,25 @@ rift_status rift_prefill(const rift_model_cfg* cfg, const rift_layer_weights* la
             float* kf = static_cast<float*>(kb);
             float* vf = static_cast<float*>(vb);
             RIFT_TRY(mark(l, 0, 0));
-            RIFT_TRY(launch_gemm_f32(hf, static_cast<const float*>(w.wq), qf, T, d, d, false, st));
-            RIFT_TRY(launch_gemm_f32(hf, static_cast<const float*>(w.wk), kf, T, d, d, false, st));
-            RIFT_TRY(launch_gemm_f32(hf, static_cast<const float*>(w.wv), vf, T, d, d, false, st));
-            RIFT_TRY(launch_rope_apply_f32(qf, rope, position_ids, max_seqlen, T, c.n_heads, c.head_dim, st));
-            RIFT_TRY(launch_rope_apply_f32(kf, rope, position_ids, max_seqlen, T, c.n_heads, c.head_dim, st));
+            RIFT_TRY(launch_gemm_f32_qkv_rope(hf, static_cast<const float*>(w.wq), static_cast<const float*>(w.wk),
+                                              static_cast<const float*>(w.wv), qf, kf, vf, rope, position_ids,
+                                              max_seqlen, T, d, c.head_dim, st));
             RIFT_TRY(mark(l, 0, 1));
             RIFT_TRY(mark(l, 1, 0));
             RIFT_TRY(launch_attention_f32(qf, kf, vf, hf, cu_seqlens, n_seq, max_seqlen, c.n_heads,
                                           c.head_dim, n_prefix, st));
             RIFT_TRY(mark(l, 1, 1));
             RIFT_TRY(mark(l, 2, 0));
-            RIFT_TRY(launch_gemm_f32(hf, static_cast<const float*>(w.wo), hidden_out, T, d, d, true, st));
+            RIFT_TRY(launch_gemm_f32_resid(hf, static_cast<const float*>(w.wo), hidden_out, T, d, d, st));
             RIFT_TRY(mark(l, 2, 1));
             RIFT_TRY(launch_rmsnorm(hidden_out, false, nullptr, w.g_ffn, false, hf, false, T, d, c.rms_eps, st));
-            float* gate = reinterpret_cast<float*>(ws + L.a);
-            float* up = reinterpret_cast<float*>(ws + L.gate2);
+            float* act = reinterpret_cast<float*>(ws + L.a);
             RIFT_TRY(mark(l, 3, 0));
-            RIFT_TRY(launch_gemm_f32(hf, static_cast<const float*>(w.w_gate), gate, T, c.ffn, d, false, st));
-            RIFT_TRY(launch_gemm_f32(hf, static_cast<const float*>(w.w_up), up, T, c.ffn, d, false, st));
-            RIFT_TRY(launch_swiglu_f32(gate, up, gate, (long long)T * c.ffn, st));
+            RIFT_TRY(launch_gemm_f32_swiglu(hf, static_cast<const float*>(w.w_gate), static_cast<const float*>(w.w_up),
+                                            act, T, c.ffn, d, st));
             RIFT_TRY(mark(l, 3, 1));
             RIFT_TRY(mark(l, 4, 0));
-            RIFT_TRY(launch_gemm_f32(gate, static_cast<const float*>(w.w_down), hidden_out, T, d, c.ffn, true, st));
+            RIFT_TRY(launch_gemm_f32_resid(act, static_cast<const float*>(w.w_down), hidden_out, T, d, c.ffn, st));
             RIFT_TRY(mark(l, 4, 1));
         }
     }

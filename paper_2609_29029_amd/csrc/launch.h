@@ -126,15 +126,13 @@ hipError_t launch_skinny_qkv(const float* part, int S, int M, int d, int hd, con
 hipError_t launch_skinny_swiglu(const float* part, int S, int M, int F, uint16_t* a, hipStream_t st);
 
 // ---------------------------------------------------------------- f32 path
-// C[M][N] = A[M][K] B[N][K]^T (+ C when accumulate)
-hipError_t launch_gemm_f32(const float* a, const float* b, float* c, int M, int N, int K,
-                           bool accumulate, hipStream_t st);
-// in-place rotate-half RoPE on x [M][H*hd] (f32)
-hipError_t launch_rope_apply_f32(float* x, const float2* rope, const int* pos, int n_pos, int M,
-                                 int n_heads, int hd, hipStream_t st);
-// a[M][F] = silu(g) * u  (f32, separate gate/up buffers; a may alias g)
-hipError_t launch_swiglu_f32(const float* g, const float* u, float* a, long long n,
-                             hipStream_t st);
+// q|k|v = a [wq|wk|wv]^T with RoPE on q and k; x += a b^T; out = silu(a wg^T) * (a wu^T)
+hipError_t launch_gemm_f32_qkv_rope(const float* a, const float* wq, const float* wk, const float* wv, float* q,
+                                    float* k, float* v, const float2* rope, const int* pos, int n_pos, int M, int d,
+                                    int hd, hipStream_t st);
+hipError_t launch_gemm_f32_resid(const float* a, const float* b, float* x, int M, int N, int K, hipStream_t st);
+hipError_t launch_gemm_f32_swiglu(const float* a, const float* wg, const float* wu, float* out, int M, int F, int K,
+                                  hipStream_t st);
 hipError_t launch_attention_f32(const float* q, const float* k, const float* v, float* o,
                                 const int* cu, int n_seq, int max_seqlen, int n_heads, int hd,
                                 int n_prefix, hipStream_t st);

@@ -1,0 +1,62 @@
+"""The float32 prefill's two GEMM kernels (a workgroup per 16 x 32 tile with K split
+over its waves, and 64 x 64 tiles) and its 16-query attention blocks, at row
+counts around their tiles: against the float64 oracle (rowwise 1e-4), weights
+and the key/value cache at 4-byte alignment, and a prompt alone bit for bit
+equal to the same prompt in a batch that runs on the other kernel."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import synth
+from oracle import rift_oracle as O
+from tests.rift_testlib import oracle_layer_weights, rowwise_rel_err, torch_mod, upload
+
+pytestmark = pytest.mark.gpu
+
+
+def unaligned(a):
+    """A device tensor of a's values that starts 4 bytes into an allocation."""
+    torch = torch_mod()
+    flat = torch.empty(a.size + 1, dtype=torch.float32, device="cuda")
+    out = flat[1:].view(a.shape)
+    out.copy_(torch.from_numpy(a))
+    return out
+
+
+@pytest.mark.parametrize("d,hd,ffn,lens,checked", [
+    (64, 64, 16, [1, 15, 16, 17, 33], 5), (128, 128, 80, [31, 2, 48], 3), (256, 64, 688, [88, 88], 2),
+    (320, 64, 48, [63, 65], 2), (1024, 128, 2064, [40] + [300] * 4, 1)])
+def test_f32_tiles_against_oracle(d, hd, ffn, lens, checked):
+    import paper_2609_29029_amd as R
+    torch = torch_mod()
+    m = synth.ModelShape(d=d, n_heads=d // hd, head_dim=hd, ffn=ffn, n_layers=1)
+    W = synth.make_layer(dataclasses.replace(synth.get("tiny"), model=m, cid=90 + hd), 0)
+    Wd = {k: (unaligned(v) if v.ndim == 2 else upload(v, "f32")) for k, v in W.items()}
+    cfg = R.model_cfg(d, d // hd, hd, ffn, 1, m.rms_eps, m.rope_base, R.RIFT_F32)
+    rng = np.random.default_rng(d + len(lens))
+    x = rng.standard_normal((sum(lens), d)).astype(np.float32)
+
+    def run(ls, xs, n_prefix=0):
+        cu = np.concatenate([[0], np.cumsum(ls)]).astype(np.int32)
+        pos = np.concatenate([np.arange(n) + (n_prefix if i else 0) for i, n in enumerate(ls)]).astype(np.int32)
+        T, L = int(cu[-1]), max(ls) + n_prefix
+        ws = torch.empty(R.rift_prefill_workspace_size(cfg, T, L), dtype=torch.uint8, device="cuda")
+        hid = torch.empty(T, d, dtype=torch.float32, device="cuda")
+        kv = unaligned(np.zeros((1, 2, T, d), np.float32))
+        R.rift_prefill(cfg, [Wd], upload(xs, "f32"), torch.from_numpy(cu).cuda(), torch.from_numpy(pos).cuda(), len(ls),
+                       L, hid, ws, kv_cache=kv, n_prefix=n_prefix)
+        torch.cuda.synchronize()
+        return hid.cpu().numpy(), kv.cpu().numpy(), cu, pos
+
+    hid, kv, cu, pos = run(lens, x)
+    ys = O.prefill(x.astype(np.float64), cu, pos, [oracle_layer_weights(W, "f32")], m.n_heads, hd, m.rms_eps, m.rope_base,
+                   list(range(checked)))
+    for i in range(checked):
+        assert rowwise_rel_err(hid[cu[i]:cu[i + 1]].astype(np.float64), ys[i]) <= 1e-4, i
+    alone = run(lens[:1], x[:lens[0]])
+    assert np.array_equal(alone[0], hid[:lens[0]]) and np.array_equal(alone[1], kv[:, :, :lens[0]])
+    # a prompt after a shared prefix of 7 rows against the two packed together
+    whole = run([7 + lens[1]], np.concatenate([x[:7], x[cu[1]:cu[2]]]))
+    split = run([7, lens[1]], np.concatenate([x[:7], x[cu[1]:cu[2]]]), n_prefix=7)
+    assert np.array_equal(whole[0], split[0]) and np.array_equal(whole[1], split[1])
