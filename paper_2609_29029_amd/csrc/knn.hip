@@ -9,8 +9,14 @@
 //   tile_gram     G_ij = the canonical float64 dot product of E_i and E_j
 //                 (8-element granules, granule g into accumulator g mod 4, then
 //                 (a0 + a2) + (a1 + a3)); the float32 products are exact in
-//                 float64, so fused multiply-adds change nothing.  16 x 16 pairs
-//                 per workgroup, 32-element chunks of both rows through LDS.
+//                 float64.  A workgroup per 16 x 16 pairs of the lower triangle (the
+//                 products commute, so the upper half is its mirror), wave q the
+//                 granules of class q on v_mfma_f64_16x16x4f64, whose four
+//                 products are fused-multiply-added in ascending k onto the
+//                 accumulator (checked bit for bit against that chain), i.e. the
+//                 canonical order.  400 tiles, d = 4,096: 150 us with one pair
+//                 per thread on the vector units before, 35 us now (49 without the
+//                 next slice's loads in flight).
 //   knn_smooth    one wave per tile: cosines G_ij / sqrt(G_ii G_jj) (0 when
 //                 that is 0) in LDS, m rounds of a wave arg-max (largest
 //                 cosine, then the lower tile), then
@@ -76,34 +82,68 @@ pool_embed_kernel(const void* __restrict__ tokens, int n_v, int d, const double*
     for (int e = 0; e < 8; ++e) out[e] = (float)P[e];
 }
 
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+
+constexpr int kGramK = 256;            // elements per LDS slice
+constexpr int kGramLd = kGramK + 4;    // row stride: the 64 lanes of an operand read hit distinct banks
+
 __global__ void __launch_bounds__(256)
 tile_gram_kernel(const float* __restrict__ emb, int n, int d, double* __restrict__ G) {
-    __shared__ float A[16][33];
-    __shared__ float B[16][33];
-    const int tid = threadIdx.x;
-    const int ti = tid & 15, tj = tid >> 4;
-    const int i0 = blockIdx.x * 16, j0 = blockIdx.y * 16;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int k = 0; k < d; k += 32) {
+    __shared__ __align__(16) float A[16 * kGramLd], B[16 * kGramLd];
+    __shared__ double fold[4][16][17];
+    // block (bi, bj), bj <= bi, of the lower triangle
+    int bi = (int)((sqrtf(8.0f * (float)blockIdx.x + 1.0f) - 1.0f) * 0.5f);
+    while ((bi + 1) * (bi + 2) / 2 <= (int)blockIdx.x) ++bi;
+    while (bi * (bi + 1) / 2 > (int)blockIdx.x) --bi;
+    const int bj = (int)blockIdx.x - bi * (bi + 1) / 2;
+    const int i0 = bi * 16, j0 = bj * 16;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int q = __builtin_amdgcn_readfirstlane(tid >> 6);   // granule class of this wave
+    const int r = lane & 15, kq = lane >> 4;
+    // thread (row tid / 16, 16 bytes tid % 16 + 16 u): the next slice of both
+    // operands is in registers while the current one is multiplied
+    const int row = tid >> 4, c0 = 4 * (tid & 15);
+    const float* arow = emb + (size_t)(i0 + row < n ? i0 + row : n - 1) * d;
+    const float* brow = emb + (size_t)(j0 + row < n ? j0 + row : n - 1) * d;
+    f32x4_t na[4], nb[4];
+    auto fetch = [&](int k0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int idx = 2 * tid + u;          // 0..511: row idx / 32, column idx % 32
-            const int r = idx >> 5, c = idx & 31;
-            const int ia = (i0 + r) < n ? (i0 + r) : n - 1;
-            const int jb = (j0 + r) < n ? (j0 + r) : n - 1;
-            A[r][c] = emb[(size_t)ia * d + k + c];
-            B[r][c] = emb[(size_t)jb * d + k + c];
+        for (int u = 0; u < 4; ++u) {
+            const int k = k0 + c0 + 64 * u < d ? k0 + c0 + 64 * u : 0;   // past the row: not used
+            na[u] = *reinterpret_cast<const f32x4_t*>(arow + k);
+            nb[u] = *reinterpret_cast<const f32x4_t*>(brow + k);
+        }
+    };
+    f64x4_t acc = {0.0, 0.0, 0.0, 0.0};
+    fetch(0);
+    for (int k0 = 0; k0 < d; k0 += kGramK) {
+        const int nk = d - k0 < kGramK ? d - k0 : kGramK;     // a multiple of 32
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            *reinterpret_cast<f32x4_t*>(A + row * kGramLd + c0 + 64 * u) = na[u];
+            *reinterpret_cast<f32x4_t*>(B + row * kGramLd + c0 + 64 * u) = nb[u];
         }
         __syncthreads();
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                acc[q] = fma((double)A[ti][8 * q + e], (double)B[tj][8 * q + e], acc[q]);
-        __syncthreads();
+        if (k0 + kGramK < d) fetch(k0 + kGramK);
+        const float* a = A + r * kGramLd + 8 * q + kq;
+        const float* b = B + r * kGramLd + 8 * q + kq;
+#pragma unroll 4
+        for (int s = 0; s < nk; s += 32) {
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[s], (double)b[s], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[s + 4], (double)b[s + 4], acc, 0, 0, 0);
+        }
     }
-    const int i = i0 + ti, j = j0 + tj;
-    if (i < n && j < n) G[(size_t)i * n + j] = (acc[0] + acc[2]) + (acc[1] + acc[3]);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) fold[q][kq + 4 * v][r] = acc[v];   // value v: row kq + 4 v, column r
+    __syncthreads();
+    const int col = tid & 15;
+    const double g = (fold[0][row][col] + fold[2][row][col]) + (fold[1][row][col] + fold[3][row][col]);
+    const int i = i0 + row, j = j0 + col;
+    if (i < n && j < n) {
+        G[(size_t)i * n + j] = g;
+        G[(size_t)j * n + i] = g;
+    }
 }
 
 __global__ void __launch_bounds__(64)
@@ -165,8 +205,9 @@ hipError_t launch_knn_smooth(const void* tokens, bool bf16, int n_tiles, int n_v
         hipLaunchKernelGGL(pool_embed_kernel<true>, pgrid, dim3(64), 0, st, tokens, n_v, d, inv, emb);
     else
         hipLaunchKernelGGL(pool_embed_kernel<false>, pgrid, dim3(64), 0, st, tokens, n_v, d, inv, emb);
-    const dim3 ggrid((n_tiles + 15) / 16, (n_tiles + 15) / 16);
-    hipLaunchKernelGGL(tile_gram_kernel, ggrid, dim3(256), 0, st, emb, n_tiles, d, gram);
+    const unsigned nb = (unsigned)((n_tiles + 15) / 16);
+    hipLaunchKernelGGL(tile_gram_kernel, dim3(nb * (nb + 1) / 2), dim3(256), 0, st, emb, n_tiles, d,
+                       gram);
     hipLaunchKernelGGL(knn_smooth_kernel, dim3(n_tiles), dim3(64), (size_t)n_tiles * (sizeof(double) + 1), st,
                        gram, n_tiles, s_raw, m, s_out);
     return hipGetLastError();
