@@ -2,7 +2,7 @@
 //
 //   prep_w       w = t - (1/M) sum_j B_j in float64, rounded to float32; also
 //                clears the per-tile arrival counters of score_tiles.
-//   score_tiles  one wave per 32 tokens of a tile (token sets of all tiles
+//   score_tiles  one wave per 32 (few tiles: 16) tokens of a tile (token sets of all tiles
 //                dealt out four to a workgroup, so the work spreads evenly over
 //                the CUs whatever the tile count).  bf16 rows are read 512
 //                contiguous bytes at a time into a per-wave LDS buffer, the next
@@ -57,6 +57,41 @@ __device__ __forceinline__ bool precedes(double ka, int ia, double kb, int ib) {
     return (ka > kb) || (ka == kb && ia < ib);
 }
 
+// Entries of the ranking's key and id arrays for n tiles: a power of two, at
+// least 4 (the counting pass reads words four at a time).
+__host__ __device__ inline int rank_slots(int n) {
+    int N = 4;
+    while (N < n) N <<= 1;
+    return N;
+}
+
+// The top 32 bits of an integer that orders like the (not NaN) score x.
+__device__ __forceinline__ uint32_t score_top(double x) {
+    const uint32_t h = (uint32_t)(__builtin_bit_cast(uint64_t, x) >> 32);
+    return h ^ ((h >> 31) ? 0xffffffffu : 0x80000000u);
+}
+
+// pos[j], j < PER: the number of tiles whose top word exceeds that of tile
+// tid + nt j, four words a step (one 16-byte LDS read that every thread
+// shares).  The pads' words are those of -inf and exceed none.
+template <int PER>
+__device__ __forceinline__ void count_above(const uint32_t* top, int n, int tid, int nt, int (&pos)[4]) {
+    uint32_t t[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int i = tid + nt * j;
+        t[j] = top[i < n ? i : 0];
+    }
+#pragma unroll 4
+    for (int m = 0; m < n; m += 4) {
+        const u32x4_t w = *reinterpret_cast<const u32x4_t*>(top + m);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int j = 0; j < PER; ++j) pos[j] += w[e] > t[j] ? 1 : 0;
+    }
+}
+
 // Rank the scene's tile scores s[0, n) with the threads of one workgroup
 // (blockDim.x threads, a multiple of 64): order by (s desc, id asc), u =
 // (s - min)/(max - min) in float64 (1 when max == min), n_keep = top-K or the
@@ -67,37 +102,59 @@ __device__ __forceinline__ bool precedes(double ka, int ia, double kb, int ib) {
 __device__ void rank_scene(const double* s, int n, int keep_count, double tau, float* __restrict__ u_out,
                            int* __restrict__ order, int* __restrict__ n_keep, double* __restrict__ s_copy,
                            unsigned char* lds) {
-    int N = 1;
-    while (N < n) N <<= 1;
+    const int N = rank_slots(n);
     double* ext = reinterpret_cast<double*>(lds);          // max, min
     int& kept = *reinterpret_cast<int*>(lds + 16);
     double* key = reinterpret_cast<double*>(lds + 32);
-    int* id = reinterpret_cast<int*>(lds + 32 + (size_t)8 * N);
+    int* id = reinterpret_cast<int*>(lds + 32 + (size_t)8 * N);            // the sort's ids, or
+    uint32_t* top = reinterpret_cast<uint32_t*>(id);                       // the counting pass's words
+    int* same = reinterpret_cast<int*>(lds + 32 + (size_t)12 * N);         // and tiles per position
     const int tid = threadIdx.x;
     const int nt = blockDim.x;
     for (int i = tid; i < N; i += nt) {
         // agent-coherent load: in the fused pass other workgroups wrote s
         const double si = i < n ? __hip_atomic_load(s + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -INFINITY;
-        key[i] = (si == si) ? si : -INFINITY;
-        id[i] = i;
+        const double k = (si == si) ? si + 0.0 : -INFINITY;   // -0 -> +0, as the comparisons have it
+        key[i] = k;
+        if (n <= 1024) {
+            top[i] = score_top(k);
+            same[i] = 0;
+        } else {
+            id[i] = i;
+        }
         if (s_copy != nullptr && i < n) s_copy[i] = si;
     }
     if (tid == 0) kept = 0;
     __syncthreads();
     int local = 0;
     if (n <= 1024) {
-        int pos[4];   // positions of this thread's tiles i = tid + nt j
+        // A tile's position is the number of tiles that precede it.  The whole
+        // call waits for this one workgroup, and float64 comparisons of every
+        // pair took 24 us at 400 tiles: so count by top words, and only tiles
+        // that share a word (and so a position) with another one compare keys.
+        int pos[4] = {0, 0, 0, 0};   // positions of this thread's tiles i = tid + nt j
+        const int per = (n + nt - 1) / nt;
+        if (tid < n) {
+            if (per <= 1) count_above<1>(top, n, tid, nt, pos);
+            else if (per == 2) count_above<2>(top, n, tid, nt, pos);
+            else count_above<4>(top, n, tid, nt, pos);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (tid + nt * j < n) atomicAdd(&same[pos[j]], 1);
+        }
+        __syncthreads();
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int i = tid + nt * j;
-            pos[j] = 0;
             if (i < n) {
                 const double ki = key[i];
-                int r = 0;
-                for (int m = 0; m < n; ++m) r += precedes(key[m], m, ki, i) ? 1 : 0;
-                pos[j] = r;
-                if (r == 0) ext[0] = ki;
-                if (r == n - 1) ext[1] = ki;
+                if (same[pos[j]] > 1) {
+                    int r = 0;
+                    for (int m = 0; m < n; ++m) r += precedes(key[m], m, ki, i) ? 1 : 0;
+                    pos[j] = r;
+                }
+                if (pos[j] == 0) ext[0] = ki;
+                if (pos[j] == n - 1) ext[1] = ki;
             }
         }
         __syncthreads();
@@ -148,18 +205,21 @@ __device__ void rank_scene(const double* s, int n, int keep_count, double tau, f
 }
 
 constexpr int kScoreWaves = 4;          // waves per workgroup
-constexpr int kScoreTok = 32;           // tokens per wave: two 16-token MFMA column blocks
 constexpr int kChunkSteps = 8;          // k-steps (32 elements each) per staged chunk: 512 bytes of a bf16 row
-constexpr int kStageBytes = kScoreTok * kChunkSteps * 64;   // one wave's LDS staging buffer (16 KB)
+// one wave's LDS staging buffer: NB 16-token blocks (NB = 2: 16 KB)
+constexpr int stage_bytes(int nb) { return 16 * nb * kChunkSteps * 64; }
 
-template <bool kBf16>
-__global__ void __launch_bounds__(64 * kScoreWaves)
+template <bool kBf16, int NB>
+__global__ void __launch_bounds__(64 * kScoreWaves, NB == 1 ? 3 : 2)
 score_tiles_kernel(const void* __restrict__ tokens, int n_tiles, int n_v, int d,
                    const void* __restrict__ qbank, int nq, const float* __restrict__ w32,
                    double* __restrict__ token_key, float* __restrict__ token_sim,
                    double* __restrict__ inv_out, int* __restrict__ arrivals, double* __restrict__ tile_score,
                    int rank, int keep_count, double tau, float* __restrict__ tile_u,
                    int* __restrict__ tile_order, int* __restrict__ n_keep, int ctl_off) {
+    constexpr int kScoreTok = 16 * NB;   // tokens per wave
+    constexpr int kStageBytes = stage_bytes(NB);
+    constexpr int NL = kScoreTok / 2;    // loads of a chunk
     extern __shared__ __align__(16) unsigned char smem[];
     float* w_lds = reinterpret_cast<float*>(smem);
 
@@ -183,15 +243,17 @@ score_tiles_kernel(const void* __restrict__ tokens, int n_tiles, int n_v, int d,
     const size_t q_off = (size_t)(r < nq ? r : nq - 1) * d;
     const int steps = d / 32;
 
-    double n2[2] = {0.0, 0.0};
-    double g[2] = {0.0, 0.0};
-    f32x4_t acc[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
+    double n2[NB] = {};
+    double g[NB] = {};
+    f32x4_t acc[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
     if constexpr (kBf16) {
-        // The wave's 32 token rows are read 512 bytes at a time: load i covers
+        // The wave's 16 NB token rows are read 512 bytes at a time: load i covers
         // rows 2i and 2i + 1 (lanes 0-31 and 32-63), 16 bytes a lane, so each
         // request is two contiguous 512-byte pieces.  The pieces go through a
-        // 16 KB LDS buffer (row lt at lt * 512, 16-byte unit j stored at unit
+        // 8 NB KB LDS buffer (row lt at lt * 512, 16-byte unit j stored at unit
         // j ^ (lt & 15)) and are read back in the MFMA B layout: for k-step s,
         // lane (r, q) takes unit 4 s + q of row 16 b + r, which the swizzle
         // spreads over distinct banks.  The next chunk's loads are in flight
@@ -201,14 +263,14 @@ score_tiles_kernel(const void* __restrict__ tokens, int n_tiles, int n_v, int d,
         unsigned char* stage = smem + (size_t)d * sizeof(float) + (size_t)wave * kStageBytes;
         const unsigned row_bytes = (unsigned)d * 2;
         const int unit = lane & 31;
-        unsigned src_row[16];   // byte offset of each loaded row in the tile (n_v * 2 d < 2^31)
+        unsigned src_row[NL];   // byte offset of each loaded row in the tile (n_v * 2 d < 2^31)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
+        for (int i = 0; i < NL; ++i) {
             const int lt = 2 * i + (lane >> 5);
             src_row[i] = (unsigned)(t0 + lt < n_v ? t0 + lt : n_v - 1) * row_bytes;
         }
         const int n_chunks = (steps + kChunkSteps - 1) / kChunkSteps;
-        u32x4_t P[16], Qc[kChunkSteps];
+        u32x4_t P[NL], Qc[kChunkSteps];
         // Issued after the query loads of the chunk being computed, so the
         // waits on those (the counter drains in order) leave these in flight.
         // Nontemporal: each token row is read exactly once.
@@ -216,7 +278,7 @@ score_tiles_kernel(const void* __restrict__ tokens, int n_tiles, int n_v, int d,
             unsigned off = (unsigned)c * 512 + (unsigned)unit * 16;
             off = off < row_bytes - 16 ? off : row_bytes - 16;   // past the row end in a partial last chunk
 #pragma unroll
-            for (int i = 0; i < 16; ++i) P[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(Xt + src_row[i] + off));
+            for (int i = 0; i < NL; ++i) P[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(Xt + src_row[i] + off));
         };
         auto load_q = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
@@ -228,7 +290,7 @@ score_tiles_kernel(const void* __restrict__ tokens, int n_tiles, int n_v, int d,
         };
         auto stage_write = [&]() __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
+            for (int i = 0; i < NL; ++i) {
                 const int lt = 2 * i + (lane >> 5);
                 *reinterpret_cast<u32x4_t*>(stage + lt * 512 + ((unit ^ (lt & 15)) << 4)) = P[i];
             }
@@ -242,7 +304,7 @@ score_tiles_kernel(const void* __restrict__ tokens, int n_tiles, int n_v, int d,
                                   (double)w1[0], (double)w1[1], (double)w1[2], (double)w1[3]};
             const bf16x8_t qa = __builtin_bit_cast(bf16x8_t, Qc[s]);
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
+            for (int b = 0; b < NB; ++b) {
                 const u32x4_t x =
                     *reinterpret_cast<const u32x4_t*>(stage + (16 * b + r) * 512 + (((4 * s + q) ^ r) << 4));
 #pragma unroll
@@ -281,9 +343,9 @@ score_tiles_kernel(const void* __restrict__ tokens, int n_tiles, int n_v, int d,
     } else {
         const float* X = static_cast<const float*>(tokens);
         const float* Q = static_cast<const float*>(qbank);
-        size_t row_off[2];
+        size_t row_off[NB];
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
+        for (int b = 0; b < NB; ++b) {
             const int t = t0 + 16 * b + r < n_v ? t0 + 16 * b + r : n_v - 1;
             row_off[b] = (tile_row0 + t) * (size_t)d;
         }
@@ -296,7 +358,7 @@ score_tiles_kernel(const void* __restrict__ tokens, int n_tiles, int n_v, int d,
             const f32x4_t qa1 = *reinterpret_cast<const f32x4_t*>(Q + q_off + k + 4);
             const float qa[8] = {qa0[0], qa0[1], qa0[2], qa0[3], qa1[0], qa1[1], qa1[2], qa1[3]};
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
+            for (int b = 0; b < NB; ++b) {
                 const f32x4_t x0 = *reinterpret_cast<const f32x4_t*>(X + row_off[b] + k);
                 const f32x4_t x1 = *reinterpret_cast<const f32x4_t*>(X + row_off[b] + k + 4);
                 const float xv[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
@@ -315,7 +377,7 @@ score_tiles_kernel(const void* __restrict__ tokens, int n_tiles, int n_v, int d,
     // r+48 hold a0..a3.  xor 32 pairs a0 with a2 and a1 with a3; xor 16 then
     // adds the two pair sums.  Every lane of the token ends with the same value.
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
+    for (int b = 0; b < NB; ++b) {
         const int tok = t0 + 16 * b + r;
         double nn = n2[b] + __shfl_xor(n2[b], 32);
         nn = nn + __shfl_xor(nn, 16);
@@ -407,12 +469,23 @@ rank_tiles_kernel(const double* __restrict__ s, int n, int keep_count, double ta
     rank_scene(s, n, keep_count, tau, u_out, order, n_keep, s_copy, rank_lds);
 }
 
-// LDS of the ranking: max, min and the kept count, then keys and ids of
-// pow2ceil(n_tiles) entries.
+// LDS of the ranking: max, min and the kept count, then keys, words or ids and
+// counts of rank_slots(n_tiles) entries (counts only where the ranking counts).
 size_t rank_lds_bytes(int n_tiles) {
-    size_t N = 1;
-    while ((int)N < n_tiles) N <<= 1;
-    return 32 + 12 * N;
+    return 32 + (n_tiles <= 1024 ? 16 : 12) * (size_t)rank_slots(n_tiles);
+}
+
+// Whether a wave takes 16 tokens instead of 32, from the workgroups that 32-token
+// sets make.  A workgroup alone on its CU takes 55 us with 32-token sets and 38
+// with 16 (d = 4,096), two on a CU 100 and 61, three of the 16-token ones 88; so 16
+// tokens pay where they still leave one workgroup a CU (8 tiles: 54 -> 38 us) and
+// where 32 would put two on some CUs and 16 at most three on any (64 tiles: 92.5 ->
+// 88; d = 1,024 36.5 -> 32).  Elsewhere 32 tokens win (100 tiles 103 against 117 us,
+// 400 tiles 370 against 403): the background direction w is widened to float64
+// once for twice the tokens.
+inline bool small_sets(long long wgs32) {
+    constexpr long long kCus = 256;
+    return 2 * wgs32 <= kCus || (wgs32 > kCus && 2 * wgs32 <= 3 * kCus);
 }
 
 hipError_t launch_score(const void* tokens, bool bf16, int n_tiles, int n_v, int d,
@@ -424,25 +497,26 @@ hipError_t launch_score(const void* tokens, bool bf16, int n_tiles, int n_v, int
     const int prep_threads = d > n_clear ? d : n_clear;
     hipLaunchKernelGGL(prep_w_kernel, dim3((prep_threads + 255) / 256), dim3(256), 0, st, qbank, bf16 ? 1 : 0,
                        d, n_bg, w32, arrivals, n_clear);
-    const long long sets = (long long)n_tiles * ((n_v + kScoreTok - 1) / kScoreTok);
-    const unsigned wgs = (unsigned)((sets + kScoreWaves - 1) / kScoreWaves);
-    // w and the staging buffers; at the end the ranking's region and, in the
-    // last 64 bytes, the control words (80 KB at d = 4096: two workgroups a CU)
-    size_t lds = (size_t)d * sizeof(float) + (bf16 ? (size_t)kScoreWaves * kStageBytes : 0);
-    const size_t rl = rank_lds_bytes(n_tiles) + 64;
-    if (lds < rl) lds = rl;
-    const int ctl_off = (int)(lds - 64);
     double* inv_out = knn_m > 0 ? inv : nullptr;
     const int rank = knn_m > 0 ? 0 : 1;   // with smoothing the ranking waits for the smoothed scores
-    if (bf16) {
-        hipLaunchKernelGGL(score_tiles_kernel<true>, dim3(wgs), dim3(64 * kScoreWaves), lds, st,
-                           tokens, n_tiles, n_v, d, qbank, 1 + n_bg, w32, token_key, token_sim, inv_out, arrivals,
-                           tile_score, rank, keep_count, tau, tile_u, tile_order, n_keep, ctl_off);
-    } else {
-        hipLaunchKernelGGL(score_tiles_kernel<false>, dim3(wgs), dim3(64 * kScoreWaves), lds, st,
-                           tokens, n_tiles, n_v, d, qbank, 1 + n_bg, w32, token_key, token_sim, inv_out, arrivals,
-                           tile_score, rank, keep_count, tau, tile_u, tile_order, n_keep, ctl_off);
-    }
+    auto launch = [&](auto kernel, int nb) {
+        const long long sets = (long long)n_tiles * ((n_v + 16 * nb - 1) / (16 * nb));
+        const unsigned wgs = (unsigned)((sets + kScoreWaves - 1) / kScoreWaves);
+        // w and the staging buffers; at the end the ranking's region and, in the
+        // last 64 bytes, the control words (d = 4096: 80 KB, two workgroups a CU,
+        // or with sets of 16 tokens 48 KB, three)
+        size_t lds = (size_t)d * sizeof(float) + (bf16 ? (size_t)kScoreWaves * stage_bytes(nb) : 0);
+        const size_t rl = rank_lds_bytes(n_tiles) + 64;
+        if (lds < rl) lds = rl;
+        hipLaunchKernelGGL(kernel, dim3(wgs), dim3(64 * kScoreWaves), lds, st, tokens, n_tiles, n_v, d, qbank, 1 + n_bg,
+                           w32, token_key, token_sim, inv_out, arrivals, tile_score, rank, keep_count, tau, tile_u,
+                           tile_order, n_keep, (int)(lds - 64));
+    };
+    const bool small = small_sets(((long long)n_tiles * ((n_v + 31) / 32) + kScoreWaves - 1) / kScoreWaves);
+    if (bf16 && small) launch(score_tiles_kernel<true, 1>, 1);
+    else if (bf16) launch(score_tiles_kernel<true, 2>, 2);
+    else if (small) launch(score_tiles_kernel<false, 1>, 1);
+    else launch(score_tiles_kernel<false, 2>, 2);
     if (knn_m > 0) {
         const hipError_t e = launch_knn_smooth(tokens, bf16, n_tiles, n_v, d, inv, emb, gram, tile_score,
                                                knn_m, s_smooth, st);
@@ -458,11 +532,14 @@ hipError_t launch_score(const void* tokens, bool bf16, int n_tiles, int n_v, int
 
 namespace rift {
 hipError_t score_init_attributes() {
-    const int bytes = 16384 * (int)sizeof(float) + kScoreWaves * kStageBytes;   // >= rank_lds_bytes(4096) + 64
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&score_tiles_kernel<true>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&score_tiles_kernel<false>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    const int bytes = 16384 * (int)sizeof(float) + kScoreWaves * stage_bytes(2);   // >= rank_lds_bytes(4096) + 64
+    hipError_t e = hipSuccess;
+    for (const void* f : {reinterpret_cast<const void*>(&score_tiles_kernel<true, 1>),
+                          reinterpret_cast<const void*>(&score_tiles_kernel<true, 2>),
+                          reinterpret_cast<const void*>(&score_tiles_kernel<false, 1>),
+                          reinterpret_cast<const void*>(&score_tiles_kernel<false, 2>)}) {
+        if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    }
+    return e;
 }
 }  // namespace rift
