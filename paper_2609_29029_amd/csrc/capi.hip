@@ -704,21 +704,22 @@ rift_status rift_prefill(const rift_model_cfg* cfg, const rift_layer_weights* la
 
 namespace {
 // decode workspace: RoPE table over max_seqlen + max_new positions, the new
-// tokens' positions, h, q, k, v [n_seq][d] and the SwiGLU activation [n_seq][ffn]
+// tokens' positions, h, q, k, v [n_seq][d], the SwiGLU activation [n_seq][ffn], the
+// GEMMs' partial sums, and the attention's work list, counters and chunk results
 struct DecodeLayout {
-    size_t rope, pos, h, q, k, v, a, part, total;
+    size_t rope, pos, h, q, k, v, a, part, n_list, list, arrived, lpart, total;
 };
 // the decode GEMMs split K (float32 partials) when every shape allows it
 bool decode_skinny(const rift_model_cfg& c) {
     return skinny_supported(3 * c.d, c.d, c.d) && skinny_supported(c.d, c.d, c.d) &&
            skinny_supported(2 * c.ffn, c.d, c.ffn) && skinny_supported(c.d, c.ffn, c.d) && skinny_norm_supported(c.d);
 }
-size_t decode_part_floats(const rift_model_cfg& c, int64_t n_seq) {
+size_t decode_gemm_floats(const rift_model_cfg& c, int64_t n_seq) {
     if (!decode_skinny(c)) return 0;
     const int64_t shapes[4][2] = {{3 * (int64_t)c.d, c.d}, {c.d, c.d}, {2 * (int64_t)c.ffn, c.d}, {c.d, c.ffn}};
     int64_t most = 0;
     for (const auto& nk : shapes) {
-        const int64_t f = (int64_t)skinny_splits((int)nk[0], (int)nk[1]) * nk[0];
+        const int64_t f = (int64_t)skinny_slots((int)nk[0], (int)nk[1]) * nk[0];
         most = f > most ? f : most;
     }
     return (size_t)(most * n_seq);
@@ -741,7 +742,16 @@ DecodeLayout decode_layout(const rift_model_cfg& c, int64_t n_seq, int64_t n_pos
     L.a = off;
     off += align_up((size_t)n_seq * c.ffn * 2);
     L.part = off;
-    off += align_up(decode_part_floats(c, n_seq) * sizeof(float));
+    off += align_up(decode_gemm_floats(c, n_seq) * sizeof(float));
+    const size_t entries = (size_t)decode_entries(n_seq, n_pos, c.n_heads, c.head_dim);
+    L.n_list = off;
+    off += align_up(sizeof(int));
+    L.list = off;
+    off += align_up(entries * sizeof(DecodeEntry));
+    L.arrived = off;
+    off += align_up((size_t)n_seq * c.n_heads * sizeof(int));
+    L.lpart = off;
+    off += align_up((size_t)decode_part_floats(n_seq, n_pos, c.n_heads, c.head_dim) * sizeof(float));
     L.total = off;
     return L;
 }
@@ -799,15 +809,25 @@ rift_status rift_decode_step(const rift_model_cfg* cfg, const rift_layer_weights
     do {                                              \
         if ((x) != hipSuccess) return RIFT_ERR_HIP;   \
     } while (0)
-    RIFT_TRY(launch_rope_table(rope, n_pos, c.head_dim, c.rope_base, st));
-    RIFT_TRY(launch_decode_pos(cu_p, n_seq, n_prefix, step, pos, st));
+    DecodeList list{};
+    list.entry = reinterpret_cast<DecodeEntry*>(ws + L.list);
+    list.n = reinterpret_cast<int*>(ws + L.n_list);
+    list.arrived = reinterpret_cast<int*>(ws + L.arrived);
+    list.part = reinterpret_cast<float*>(ws + L.lpart);
+    DecodeQkv qkv{};
+    RIFT_TRY(launch_decode_prep(cu_p, n_seq, c.n_heads, c.head_dim, total_tokens, n_prefix, step, n_pos, c.rope_base,
+                                rope, pos, list, st));
     if (decode_skinny(c)) {
         // split-K GEMMs; the residual reduce of each layer's last GEMM also
         // applies the next layer's attention RMSNorm
         float* part = reinterpret_cast<float*>(ws + L.part);
         const int F = c.ffn;
-        const int s_qkv = skinny_splits(3 * d, d), s_o = skinny_splits(d, d);
-        const int s_gu = skinny_splits(2 * F, d), s_dn = skinny_splits(d, F);
+        const SkinnySplit s_o = skinny_split(d, d), s_gu = skinny_split(2 * F, d), s_dn = skinny_split(d, F);
+        qkv.part = part;
+        qkv.sp = skinny_split(3 * d, d);
+        qkv.rope = rope;
+        qkv.pos = pos;
+        qkv.n_pos = n_pos;
         RIFT_TRY(launch_rmsnorm(x_new, true, hidden_out, layers[0].g_attn, true, h, true, n_seq, d, c.rms_eps, st));
         for (int l = 0; l < c.n_layers; ++l) {
             const rift_layer_weights& w = layers[l];
@@ -815,12 +835,10 @@ rift_status rift_decode_step(const rift_model_cfg* cfg, const rift_layer_weights
             uint16_t* vn = static_cast<uint16_t*>(kv_new) + (size_t)(2 * l + 1) * nd;
             RIFT_TRY(launch_skinny_gemm(h, static_cast<const uint16_t*>(w.wq), static_cast<const uint16_t*>(w.wk),
                                         static_cast<const uint16_t*>(w.wv), d, n_seq, 3 * d, d, part, st));
-            RIFT_TRY(launch_skinny_qkv(part, s_qkv, n_seq, d, c.head_dim, rope, pos, n_pos, qb, kn, vn, max_new,
-                                       step, st));
-            RIFT_TRY(launch_decode_attention(qb, static_cast<const uint16_t*>(kv_cache) + (size_t)(2 * l) * td,
+            RIFT_TRY(launch_decode_attention(nullptr, qkv, static_cast<const uint16_t*>(kv_cache) + (size_t)(2 * l) * td,
                                              static_cast<const uint16_t*>(kv_cache) + (size_t)(2 * l + 1) * td, kn,
                                              vn, cu_p, n_seq, total_tokens, n_prefix, c.n_heads, c.head_dim,
-                                             n_pos, max_new, step, h, st));
+                                             n_pos, max_new, step, list, h, st));
             RIFT_TRY(launch_skinny_gemm(h, static_cast<const uint16_t*>(w.wo), nullptr, nullptr, d, n_seq, d, d,
                                         part, st));
             RIFT_TRY(launch_skinny_resid_norm(part, s_o, n_seq, d, hidden_out, static_cast<const uint16_t*>(w.g_ffn),
@@ -863,8 +881,8 @@ rift_status rift_decode_step(const rift_model_cfg* cfg, const rift_layer_weights
         qa.hd = c.head_dim;
         RIFT_TRY(launch_gemm_qkv_rope(qa, st));
         RIFT_TRY(launch_kv_append(kb, vb, kn, vn, n_seq, d, max_new, step, st));
-        RIFT_TRY(launch_decode_attention(qb, kp, vp, kn, vn, cu_p, n_seq, total_tokens, n_prefix, c.n_heads,
-                                         c.head_dim, n_pos, max_new, step, h, st));
+        RIFT_TRY(launch_decode_attention(qb, qkv, kp, vp, kn, vn, cu_p, n_seq, total_tokens, n_prefix, c.n_heads,
+                                         c.head_dim, n_pos, max_new, step, list, h, st));
         RIFT_TRY(launch_gemm_resid(h, static_cast<const uint16_t*>(w.wo), hidden_out, n_seq, d, d, st));
         RIFT_TRY(launch_rmsnorm(hidden_out, false, nullptr, w.g_ffn, true, h, true, n_seq, d, c.rms_eps, st));
         RIFT_TRY(launch_gemm_swiglu(h, static_cast<const uint16_t*>(w.w_gate), static_cast<const uint16_t*>(w.w_up),

@@ -7,17 +7,30 @@
 // decoder layers are those of the prefill (Sec. 2.1; LLaMA-7B shape); the
 // per-token GEMMs run on the prefill's kernels with M = n_seq.
 //
-//   decode_pos     position of each prompt's new token, L_i + step
+//   decode_prep    position of each prompt's new token, L_i + step; the RoPE
+//                  table; the attention's work list and cleared counters
 //   kv_append      this step's rotated key and value rows into slot `step`
-//   decode_attn    one workgroup (4 waves) per (prompt, head), the HD / 8
-//                  lanes of each row group reading one key or value row of
-//                  2 HD bytes whole (HD = 128: 16 lanes, 16 groups; HD = 64: 8
-//                  lanes, 32 groups): scores of every key in LDS (a dot
-//                  product per group, summed over its lanes); the max and the
-//                  sum of 2^(s - max) over the workgroup; then the weighted sum
-//                  of the values, each lane 8 of the HD dimensions over its
-//                  group's keys, the group sums added in fixed order; output
-//                  rounded to bfloat16.
+//   decode_attn    4 waves per (prompt, head), or per (prompt, part of its keys,
+//                  head) where the prompts are few.  A prompt's keys are dealt
+//                  to 4, or for more than 256 (HD = 64: 512) keys up to 32,
+//                  streams in rounds of 32 (64) keys; a wave runs a stream
+//                  with all of a round's keys and values in flight at once,
+//                  the HD / 8 lanes of a row group reading one row of 2 HD
+//                  bytes whole, and keeps the max of the scores, the sum of
+//                  2^(s - max) and the weighted sum of the values in
+//                  registers.  The streams are joined in their order, from
+//                  LDS, or in the workgroup that arrives last.  They depend on
+//                  the prompt's own length only, so its result does not depend
+//                  on the other prompts nor on the split.
+//                  After the split-K q, k, v product the kernel also adds its
+//                  partial sums and rotates its head of q and k while the
+//                  keys arrive.
+//
+// Bound by a round's latency where prompts are few, by the cache's bytes where
+// they are many.  One prompt of 647 keys, 32 heads: 24 us + 4.7 for the q, k, v
+// reduction -> 9 (two passes over the keys by one workgroup a head before); 100 of
+// 100 to 650 keys (364 MB): 57 + 5.3 -> 67 (5.4 TB/s), and with each prompt split as
+// if alone 74.
 #include "launch.h"
 #include "rift_common.h"
 
@@ -25,12 +38,83 @@ namespace rift {
 
 namespace {
 
+// loads of keys, and of values, per wave and round, and the keys they hold
+constexpr int kLoads = 4;
+template <int HD>
+constexpr int kWaveKeys = kLoads * (64 / (HD / 8));
+template <int HD>
+constexpr int kChunk = 4 * kWaveKeys<HD>;
+constexpr int kMaxParts = 8;
+
+// Parts of a prompt's keys, four streams each.
+__host__ __device__ inline int key_parts(int nk, int chunk) {
+    return nk <= 2 * chunk ? 1 : min((nk + chunk - 1) / chunk, kMaxParts);
+}
+
+// Rows of prompt `seq` in the prefill cache: first row s0, L of them (none where
+// the offsets are not in the cache), and its keys: prefix rows, own rows and
+// generated ones, at most max_keys.
+struct PromptKeys {
+    int s0, L, nk;
+};
+__device__ __forceinline__ PromptKeys prompt_keys(const int* __restrict__ cu, int seq, int T, int P, int step, int max_keys) {
+    PromptKeys k;
+    k.s0 = cu[seq];
+    k.L = cu[seq + 1] - k.s0;
+    if (k.s0 < 0 || k.L < 0 || k.s0 + k.L > T) k.s0 = k.L = 0;
+    k.nk = min(P + k.L + step + 1, max_keys);
+    return k;
+}
+
 // cu: the prompts' own row offsets (after the shared prefix sequence when
-// n_prefix > 0)
-__global__ void decode_pos_kernel(const int* __restrict__ cu, int n_seq, int n_prefix, int step,
-                                  int* __restrict__ pos) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n_seq) pos[i] = n_prefix + (cu[i + 1] - cu[i]) + step;
+// n_prefix > 0).  Workgroup 0 the positions, counters and work list, the others
+// the RoPE table.
+__global__ void __launch_bounds__(256)
+decode_prep_kernel(const int* __restrict__ cu, int n_seq, int n_heads, int T, int n_prefix, int step, int max_keys,
+                   int chunk, int whole, double base, int hd, float2* __restrict__ rope, int* __restrict__ pos,
+                   DecodeList list) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (blockIdx.x > 0) {
+        const int half = hd >> 1;
+        const long long i = (long long)(blockIdx.x - 1) * 256 + tid;
+        if (i < (long long)max_keys * half) rope[i] = rope_entry((int)(i / half), (int)(i % half), hd, base);
+        return;
+    }
+    __shared__ int sums[4];
+    for (int i = tid; i < n_seq * n_heads; i += 256) list.arrived[i] = 0;
+    int at = 0;   // entries of the prompts before i0
+    for (int i0 = 0; i0 < n_seq; i0 += 256) {
+        const int i = i0 + tid;
+        int c = 0;
+        DecodeEntry w{};
+        if (i < n_seq) {
+            w.pos = n_prefix + (cu[i + 1] - cu[i]) + step;
+            pos[i] = w.pos;
+            const PromptKeys k = prompt_keys(cu, i, T, n_prefix, step, max_keys);
+            w.seq = i;
+            w.s0 = k.s0;
+            w.L = k.L;
+            w.nk = k.nk;
+            w.parts = key_parts(k.nk, chunk);
+            c = whole ? 1 : w.parts;
+        }
+        int incl = c;
+        for (int s = 1; s < 64; s <<= 1) {
+            const int o = __shfl_up(incl, s);
+            if (lane >= s) incl += o;
+        }
+        if (lane == 63) sums[wave] = incl;
+        __syncthreads();
+        int before = at;
+        for (int w = 0; w < wave; ++w) before += sums[w];
+        at += sums[0] + sums[1] + sums[2] + sums[3];
+        for (int e = 0; e < c; ++e) {
+            w.part = e;
+            list.entry[before + incl - c + e] = w;
+        }
+        __syncthreads();
+    }
+    if (tid == 0) *list.n = at;
 }
 
 // 16-byte words of row i of k and v into slot `step` of prompt i
@@ -59,133 +143,303 @@ __device__ __forceinline__ float group_sum(float v) {
     return v;
 }
 
-// Keys are visited in blocks of NS kDecU keys: slot s = (64 / G) wave +
-// lane / G of the NS = 256 / G row groups takes keys j0 + NS u + s, u < kDecU,
-// and the G lanes of a group read one row, lane c its bytes 16 c .. 16 c + 15
-// (dims 8 c .. 8 c + 7).
-constexpr int kDecU = 4;
+struct DecodeAttnParams {
+    const bf16_t* q;
+    DecodeQkv qkv;
+    const bf16_t *kp, *vp;
+    bf16_t *kn, *vn;
+    const int* cu;
+    int n_seq, T, P, H, max_keys, max_new, step;
+    float scale_log2;
+    int whole;             // a workgroup takes all parts of a prompt
+    DecodeList list;
+    bf16_t* o;
+};
 
-template <int HD>
-__global__ void __launch_bounds__(256)
-decode_attn_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ kp, const bf16_t* __restrict__ vp,
-                   const bf16_t* __restrict__ kn, const bf16_t* __restrict__ vn, const int* __restrict__ cu,
-                   int n_seq, int T, int n_prefix, int H, int max_keys, int max_new, int step, float scale_log2,
-                   bf16_t* __restrict__ o) {
-    constexpr int G = HD / 8;        // lanes per row group
-    constexpr int NS = 256 / G;      // row groups (key slots) per workgroup
-    extern __shared__ float sc[];   // one score per key
-    __shared__ float red[4];
-    __shared__ float part[4][HD];
-    const int seq = blockIdx.x / H;
-    const int head = blockIdx.x % H;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// m is the reference of the exponentials; a part without a key has none
+__device__ __forceinline__ float exp2_ref(float s, float m) {
+    return __builtin_amdgcn_exp2f(s - (m == -INFINITY ? 0.f : m));
+}
+
+// The work list is read through pointers of its own, so that its uniform loads
+// are scalar ones.
+template <int HD, bool FUSED>
+__global__ void __launch_bounds__(256, 4)
+decode_attn_kernel(DecodeAttnParams p, const int* __restrict__ n_entries, const DecodeEntry* __restrict__ entries) {
+    constexpr int G = HD / 8;             // lanes per row group
+    constexpr int RPL = 64 / G;           // rows per load
+    constexpr int U = kLoads;
+    constexpr int KW = kWaveKeys<HD>, CH = kChunk<HD>;
+    constexpr int ST = HD + 2;            // a stream's weighted values, max and sum
+    __shared__ __align__(16) float qs[HD];
+    __shared__ __align__(16) bf16_t kvs[2][HD];   // the new token's key and value
+    __shared__ float streams[4 * kMaxParts][ST];
+    __shared__ int last;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane % G;
-    const int slot = (64 / G) * wave + lane / G;
-    int s0 = cu[seq];
-    int L = cu[seq + 1] - s0;
-    if (s0 < 0 || L < 0 || s0 + L > T) s0 = L = 0;   // offsets outside the prefill cache: no prompt keys
-    const int P = n_prefix;                           // shared prefix rows [0, P) of the cache
-    // prefix keys, the prompt's own keys, then the generated ones (at most
-    // max_keys, the LDS size)
-    const int nk = min(P + L + step + 1, max_keys);
-    const int ld = H * HD;
-    const size_t hoff = (size_t)head * HD + 8 * c;
-    auto row = [&](int j, const bf16_t* prompt_base, const bf16_t* new_base) -> const u32x4_t* {
-        return reinterpret_cast<const u32x4_t*>(
-            j < P ? prompt_base + (size_t)j * ld + hoff
-                  : (j < P + L ? prompt_base + (size_t)(s0 + j - P) * ld + hoff
-                               : new_base + ((size_t)seq * max_new + (j - P - L)) * ld + hoff));
-    };
-    float qf[8];
-    {
-        const u32x4_t qw = *reinterpret_cast<const u32x4_t*>(q + (size_t)seq * ld + hoff);
+    const int ld = p.H * HD;
+    const int n_work = *n_entries * p.H;
+    for (int item = blockIdx.x; item < n_work; item += gridDim.x) {
+        const int e = item / p.H, head = item - e * p.H;
+        const DecodeEntry w = entries[e];
+        const int seq = w.seq, n_parts = w.parts;
+        const int part0 = p.whole ? 0 : w.part, part1 = p.whole ? n_parts : w.part + 1;
+        const int nk = w.nk, P = p.P, L = w.L, s0 = w.s0;
+        const int jnew = P + L + p.step;          // the new token's key (past nk: not attended)
+        const int new_part = (jnew / KW) % (4 * n_parts) / 4;
+        const bool tail = part0 <= new_part && new_part < part1;   // it is in this workgroup's streams
+        const size_t hoff = (size_t)head * HD + 8 * c;
+        // The new token's q, and with its key the k and v: wave (region) 0, 1, 2,
+        // lane j owning column j of the head and its rotate-half partner.
+        // (The other waves and lanes load what wave 0 does: a branch here would
+        // have the compiler wait for these loads before the keys' are issued.)
+        constexpr int kPart = 4;                  // partial sums in flight
+        float a1[kPart], a2[kPart];
+        float2 cs;
+        const bool mine = FUSED && lane < HD / 2 && wave < (tail ? 3 : 1);
+        const float* p0;
+        int slots;
+        const size_t slot_ld = (size_t)p.n_seq * (3 * ld);
+        if constexpr (FUSED) {
+            const int region = wave < (tail ? 3 : 1) ? wave : 0;
+            const int col = region * ld + head * HD, pl = lane & (HD / 2 - 1);
+            p0 = p.qkv.part + (size_t)seq * (3 * ld) + col + pl;
+            slots = p.qkv.sp.slots(col >> 7);
+            const int ps = w.pos < 0 ? 0 : (w.pos >= p.qkv.n_pos ? p.qkv.n_pos - 1 : w.pos);
+            cs = p.qkv.rope[(size_t)ps * (HD / 2) + pl];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            qf[2 * e] = bf16_lo(qw[e]);
-            qf[2 * e + 1] = bf16_hi(qw[e]);
-        }
-    }
-    // scores (base-2 logits), and the running max of this lane's keys
-    float mx = -INFINITY;
-    for (int j0 = 0; j0 < nk; j0 += NS * kDecU) {
-        u32x4_t kw[kDecU];
-#pragma unroll
-        for (int u = 0; u < kDecU; ++u)
-            kw[u] = __builtin_nontemporal_load(row(min(j0 + NS * u + slot, nk - 1), kp, kn));
-#pragma unroll
-        for (int u = 0; u < kDecU; ++u) {
-            float acc = 0.f;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                acc = fmaf(bf16_lo(kw[u][e]), qf[2 * e], acc);
-                acc = fmaf(bf16_hi(kw[u][e]), qf[2 * e + 1], acc);
-            }
-            const float sl = group_sum<G>(acc) * scale_log2;
-            const int j = j0 + NS * u + slot;
-            if (j < nk) {
-                mx = fmaxf(mx, sl);
-                if (c == 0) sc[j] = sl;
+            for (int i = 0; i < kPart; ++i) {   // past the last slot: its value, not added
+                const float* pi = p0 + min(i, slots - 1) * slot_ld;
+                a1[i] = pi[0];
+                a2[i] = pi[HD / 2];
             }
         }
-    }
-    for (int s = 32; s >= 1; s >>= 1) mx = fmaxf(mx, __shfl_xor(mx, s));
-    if (lane == 0) red[wave] = mx;
-    __syncthreads();
-    const float m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    __syncthreads();
-    float sum = 0.f;
-    for (int j = tid; j < nk; j += blockDim.x) {
-        const float p = __builtin_amdgcn_exp2f(sc[j] - m);
-        sc[j] = p;
-        sum += p;
-    }
-    for (int s = 32; s >= 1; s >>= 1) sum += __shfl_xor(sum, s);
-    if (lane == 0) red[wave] = sum;
-    __syncthreads();
-    const float inv = 1.0f / ((red[0] + red[1]) + (red[2] + red[3]));
-    // weighted values over the same key slots; lane c accumulates dims 8 c .. 8 c + 7
-    float acc[8];
+        // Stream 4 part + wave: rounds of KW keys from (4 part + wave) KW on, n_parts CH
+        // apart, the lane's u-th key j0 + RPL u of its round.
+        int part = part0, r0 = part0 * CH + wave * KW;
+        u32x4_t kw[U], vw[U];
+        auto at = [&](int j, const bf16_t* prompt_base, const bf16_t* new_base) __attribute__((always_inline)) {
+            const bool old = j < P + L;
+            const int r = old ? (j < P ? j : s0 + j - P) : seq * p.max_new + (j - P - L);
+            return reinterpret_cast<const u32x4_t*>((old ? prompt_base : new_base) +
+                                                    ((size_t)(unsigned)r * (unsigned)ld + hoff));
+        };
+        auto load_k = [&](int j0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-    for (int j0 = 0; j0 < nk; j0 += NS * kDecU) {
-        u32x4_t vw[kDecU];
+            for (int u = 0; u < U; ++u) kw[u] = __builtin_nontemporal_load(at(min(j0 + RPL * u, nk - 1), p.kp, p.kn));
+        };
+        auto load_v = [&](int j0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < kDecU; ++u)
-            vw[u] = __builtin_nontemporal_load(row(min(j0 + NS * u + slot, nk - 1), vp, vn));
+            for (int u = 0; u < U; ++u) vw[u] = __builtin_nontemporal_load(at(min(j0 + RPL * u, nk - 1), p.vp, p.vn));
+        };
+        // (a stream without keys loads the last row: with a branch the wait for the
+        // partial sums would be one for all keys and values)
+        load_k(r0 + lane / G);
+        load_v(r0 + lane / G);
+        float qf[8];
+        if constexpr (FUSED) {
+            if (mine) {
+                float x1 = a1[0], x2 = a2[0];
 #pragma unroll
-        for (int u = 0; u < kDecU; ++u) {
-            const int j = j0 + NS * u + slot;
-            if (j < nk) {
-                const float p = sc[j];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    acc[2 * e] = fmaf(p, bf16_lo(vw[u][e]), acc[2 * e]);
-                    acc[2 * e + 1] = fmaf(p, bf16_hi(vw[u][e]), acc[2 * e + 1]);
+                for (int i = 1; i < kPart; ++i)
+                    if (i < slots) {
+                        x1 += a1[i];
+                        x2 += a2[i];
+                    }
+                for (int s = kPart; s < slots; ++s) {
+                    x1 += p0[s * slot_ld];
+                    x2 += p0[s * slot_ld + HD / 2];
+                }
+                float y1 = x1, y2 = x2;
+                if (wave < 2) {
+                    y1 = x1 * cs.x - x2 * cs.y;
+                    y2 = x2 * cs.x + x1 * cs.y;
+                }
+                const bf16_t o1 = f32_to_bf16(y1), o2 = f32_to_bf16(y2);
+                if (wave == 0) {
+                    qs[lane] = bf16_to_f32(o1);
+                    qs[lane + HD / 2] = bf16_to_f32(o2);
+                } else {
+                    bf16_t* dst = (wave == 1 ? p.kn : p.vn) + ((size_t)seq * p.max_new + p.step) * ld + head * HD + lane;
+                    dst[0] = kvs[wave - 1][lane] = o1;
+                    dst[HD / 2] = kvs[wave - 1][lane + HD / 2] = o2;
                 }
             }
+            __syncthreads();
+            const f32x4_t qa = *reinterpret_cast<const f32x4_t*>(qs + 8 * c);
+            const f32x4_t qb = *reinterpret_cast<const f32x4_t*>(qs + 8 * c + 4);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                qf[i] = qa[i];
+                qf[4 + i] = qb[i];
+            }
+        } else {
+            const u32x4_t qw = *reinterpret_cast<const u32x4_t*>(p.q + (size_t)seq * ld + hoff);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                qf[2 * i] = bf16_lo(qw[i]);
+                qf[2 * i + 1] = bf16_hi(qw[i]);
+            }
         }
-    }
-    // the row groups of a wave, then the four waves, in fixed order
+        float m = -INFINITY, l = 0.f, acc[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
+        for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+        for (;;) {
+            const int j0 = r0 + lane / G;
+            int next = r0 + n_parts * CH, next_part = part;
+            if (next >= nk) {
+                ++next_part;
+                next = next_part * CH + wave * KW;
+            }
+            const bool more = next_part < part1;
+            if (FUSED && r0 <= jnew && jnew < r0 + KW) {   // the new token's rows come from LDS
+                const u32x4_t kx = *reinterpret_cast<const u32x4_t*>(&kvs[0][8 * c]);
+                const u32x4_t vx = *reinterpret_cast<const u32x4_t*>(&kvs[1][8 * c]);
 #pragma unroll
-        for (int sh = G; sh < 64; sh <<= 1) acc[e] += __shfl_xor(acc[e], sh);
-    if (lane < G) {
+                for (int u = 0; u < U; ++u)
+                    if (j0 + RPL * u == jnew) {
+                        kw[u] = kx;
+                        vw[u] = vx;
+                    }
+            }
+            // scores (base-2 logits) of the round's keys and their max
+            float sc[U];
+            float mr = m;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) part[wave][8 * c + e] = acc[e];
-    }
-    __syncthreads();
-    if (tid < HD) {
-        const float r = ((part[0][tid] + part[1][tid]) + part[2][tid]) + part[3][tid];
-        o[(size_t)seq * ld + (size_t)head * HD + tid] = f32_to_bf16(r * inv);
+            for (int u = 0; u < U; ++u) {
+                float a = 0.f;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    a = fmaf(bf16_lo(kw[u][i]), qf[2 * i], a);
+                    a = fmaf(bf16_hi(kw[u][i]), qf[2 * i + 1], a);
+                }
+                a = group_sum<G>(a) * p.scale_log2;
+                sc[u] = j0 + RPL * u < nk ? a : -INFINITY;
+                mr = fmaxf(mr, sc[u]);
+            }
+            load_k(next + lane / G);   // past the last round too, the last row (a branch would make the waits coarser)
+#pragma unroll
+            for (int s = G; s < 64; s <<= 1) mr = fmaxf(mr, __shfl_xor(mr, s));
+            const float f = exp2_ref(m, mr);
+            l *= f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[i] *= f;
+            m = mr;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (j0 + RPL * u < nk) {
+                    const float pr = exp2_ref(sc[u], m);
+                    l += pr;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        acc[2 * i] = fmaf(pr, bf16_lo(vw[u][i]), acc[2 * i]);
+                        acc[2 * i + 1] = fmaf(pr, bf16_hi(vw[u][i]), acc[2 * i + 1]);
+                    }
+                }
+            }
+            load_v(next + lane / G);
+            if (next_part != part) {   // the stream's end: its row groups in fixed order
+#pragma unroll
+                for (int s = G; s < 64; s <<= 1) {
+                    l += __shfl_xor(l, s);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) acc[i] += __shfl_xor(acc[i], s);
+                }
+                float* st = streams[4 * (part - part0) + wave];
+                if (lane < G) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) st[8 * c + i] = acc[i];
+                    if (lane == 0) {
+                        st[HD] = m;
+                        st[HD + 1] = l;
+                    }
+                }
+                m = -INFINITY;
+                l = 0.f;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+            }
+            if (!more) break;
+            part = next_part;
+            r0 = next;
+        }
+        __syncthreads();
+        const int n_streams = 4 * n_parts;
+        auto join = [&]() __attribute__((always_inline)) {
+            if (tid < HD) {
+                float mx = -INFINITY, L = 0.f, A = 0.f;
+                for (int i = 0; i < n_streams; ++i) mx = fmaxf(mx, streams[i][HD]);
+                for (int i = 0; i < n_streams; ++i) {
+                    const float f = exp2_ref(streams[i][HD], mx);
+                    L = fmaf(f, streams[i][HD + 1], L);
+                    A = fmaf(f, streams[i][tid], A);
+                }
+                p.o[(size_t)seq * ld + (size_t)head * HD + tid] = f32_to_bf16(A * (1.0f / L));
+            }
+        };
+        if (part1 - part0 == n_parts) {
+            join();
+            __syncthreads();   // LDS free for the next item
+            continue;
+        }
+        // The chunk's result crosses workgroups, possibly on other XCDs, whose L2
+        // caches are not kept coherent: agent-coherent stores and loads around an
+        // atomic count, every wave's stores complete before the count.
+        float* all = p.list.part + ((size_t)(e - w.part) * p.H + head) * (4 * ST);   // of part 0; part i: i H 4 ST on
+        const size_t part_ld = (size_t)p.H * (4 * ST);
+        for (int i = tid; i < 4 * ST; i += 256)
+            __hip_atomic_store(all + w.part * part_ld + i, streams[0][i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) {
+            int* n_arrived = p.list.arrived + (size_t)seq * p.H + head;
+            last = atomicAdd(n_arrived, 1) == n_parts - 1;
+            if (last) __hip_atomic_store(n_arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next layer
+        }
+        __syncthreads();
+        if (last) {
+            constexpr int kIt = (4 * ST + 255) / 256;   // all of a thread's loads are in flight
+            float t[kMaxParts][kIt];
+#pragma unroll
+            for (int q = 0; q < kMaxParts; ++q)
+#pragma unroll
+                for (int i = 0; i < kIt; ++i)
+                    t[q][i] = __hip_atomic_load(all + min(q, n_parts - 1) * part_ld + min(tid + 256 * i, 4 * ST - 1),
+                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int q = 0; q < kMaxParts; ++q)
+#pragma unroll
+                for (int i = 0; i < kIt; ++i)
+                    if (q < n_parts && tid + 256 * i < 4 * ST) streams[4 * q][tid + 256 * i] = t[q][i];
+            __syncthreads();
+            join();
+        }
+        __syncthreads();
     }
 }
 
 }  // namespace
 
-hipError_t launch_decode_pos(const int* cu, int n_seq, int n_prefix, int step, int* pos, hipStream_t st) {
-    hipLaunchKernelGGL(decode_pos_kernel, dim3((n_seq + 255) / 256), dim3(256), 0, st, cu, n_seq, n_prefix, step,
-                       pos);
+int decode_chunk(int hd) { return hd == 128 ? kChunk<128> : kChunk<64>; }
+
+// A workgroup takes a prompt whole where that gives each CU four.
+static bool whole_prompts(int64_t n_seq, int n_heads) { return n_seq * n_heads >= 1024; }
+
+int64_t decode_entries(int64_t n_seq, int64_t max_keys, int n_heads, int hd) {
+    return whole_prompts(n_seq, n_heads) ? n_seq : n_seq * key_parts((int)max_keys, decode_chunk(hd));
+}
+int64_t decode_part_floats(int64_t n_seq, int64_t max_keys, int n_heads, int hd) {
+    return whole_prompts(n_seq, n_heads) ? 0 : decode_entries(n_seq, max_keys, n_heads, hd) * n_heads * 4 * (hd + 2);
+}
+
+hipError_t launch_decode_prep(const int* cu, int n_seq, int n_heads, int hd, int T, int n_prefix, int step,
+                              int max_keys, double rope_base, float2* rope, int* pos, const DecodeList& list,
+                              hipStream_t st) {
+    if (hd != 64 && hd != 128) return hipErrorInvalidValue;
+    const long long n = (long long)max_keys * (hd / 2);
+    hipLaunchKernelGGL(decode_prep_kernel, dim3((unsigned)(1 + (n + 255) / 256)), dim3(256), 0, st, cu, n_seq, n_heads, T,
+                       n_prefix, step, max_keys, decode_chunk(hd), whole_prompts(n_seq, n_heads) ? 1 : 0, rope_base, hd, rope, pos, list);
     return hipGetLastError();
 }
 
@@ -199,19 +453,38 @@ hipError_t launch_kv_append(const uint16_t* k, const uint16_t* v, uint16_t* kc, 
     return hipGetLastError();
 }
 
-hipError_t launch_decode_attention(const uint16_t* q, const uint16_t* kp, const uint16_t* vp, const uint16_t* kn,
-                                   const uint16_t* vn, const int* cu, int n_seq, int T, int n_prefix, int n_heads,
-                                   int hd, int max_keys, int max_new, int step, uint16_t* o, hipStream_t st) {
+hipError_t launch_decode_attention(const uint16_t* q, const DecodeQkv& qkv, const uint16_t* kp, const uint16_t* vp,
+                                   uint16_t* kn, uint16_t* vn, const int* cu, int n_seq, int T, int n_prefix,
+                                   int n_heads, int hd, int max_keys, int max_new, int step, const DecodeList& list,
+                                   uint16_t* o, hipStream_t st) {
     if (hd != 64 && hd != 128) return hipErrorInvalidValue;
-    const float scale_log2 = 1.4426950408889634f / sqrtf((float)hd);
-    const dim3 grid((unsigned)(n_seq * n_heads));
-    const size_t lds = (size_t)max_keys * sizeof(float);
-    if (hd == 128)
-        hipLaunchKernelGGL(decode_attn_kernel<128>, grid, dim3(256), lds, st, q, kp, vp, kn, vn, cu, n_seq, T,
-                           n_prefix, n_heads, max_keys, max_new, step, scale_log2, o);
-    else
-        hipLaunchKernelGGL(decode_attn_kernel<64>, grid, dim3(256), lds, st, q, kp, vp, kn, vn, cu, n_seq, T,
-                           n_prefix, n_heads, max_keys, max_new, step, scale_log2, o);
+    DecodeAttnParams p{};
+    p.q = q;
+    p.qkv = qkv;
+    p.kp = kp;
+    p.vp = vp;
+    p.kn = kn;
+    p.vn = vn;
+    p.cu = cu;
+    p.n_seq = n_seq;
+    p.T = T;
+    p.P = n_prefix;
+    p.H = n_heads;
+    p.max_keys = max_keys;
+    p.max_new = max_new;
+    p.step = step;
+    p.scale_log2 = 1.4426950408889634f / sqrtf((float)hd);
+    p.list = list;
+    p.o = o;
+    p.whole = whole_prompts(n_seq, n_heads) ? 1 : 0;
+    int64_t wgs = decode_entries(n_seq, max_keys, n_heads, hd) * n_heads;   // those past the list's end leave
+    if (wgs > (1 << 20)) wgs = 1 << 20;
+    const dim3 grid((unsigned)wgs);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, p, list.n, list.entry); };
+    if (hd == 128 && qkv.part) launch(decode_attn_kernel<128, true>);
+    else if (hd == 128) launch(decode_attn_kernel<128, false>);
+    else if (qkv.part) launch(decode_attn_kernel<64, true>);
+    else launch(decode_attn_kernel<64, false>);
     return hipGetLastError();
 }
 

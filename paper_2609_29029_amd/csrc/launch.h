@@ -95,35 +95,73 @@ hipError_t launch_attention_worklist(const int* cu, int n_seq, int n_heads, int2
                                      hipStream_t st);
 
 // ---------------------------------------------------------------- decode (bf16)
-// pos[i] = (cu[i+1] - cu[i]) + step
-hipError_t launch_decode_pos(const int* cu, int n_seq, int n_prefix, int step, int* pos, hipStream_t st);
+// What a decode step needs before its layers: pos[i] = (keys of prompt i) - 1, the
+// position of its new token; the RoPE table (as launch_rope_table); the
+// attention's work list, one entry per workgroup and head; and n_seq * n_heads
+// arrival counters cleared.  List and partial results have decode_entries and
+// decode_part_floats elements at most.
+int decode_chunk(int hd);
+int64_t decode_entries(int64_t n_seq, int64_t max_keys, int n_heads, int hd);
+int64_t decode_part_floats(int64_t n_seq, int64_t max_keys, int n_heads, int hd);
+struct alignas(32) DecodeEntry {
+    int seq, part, parts;   // part `part` of the prompt's `parts`, or the first of all of them
+    int s0, L, nk, pos;     // its first row and rows in the prefill cache, its keys, the new token's position
+};
+struct DecodeList {
+    DecodeEntry* entry;   // a prompt's parts in order
+    int* n;
+    int* arrived;     // [n_seq][n_heads], 0 between launches
+    float* part;      // [entries][n_heads][4][hd + 2]: a stream's weighted values, max, sum
+};
+hipError_t launch_decode_prep(const int* cu, int n_seq, int n_heads, int hd, int T, int n_prefix, int step,
+                              int max_keys, double rope_base, float2* rope, int* pos, const DecodeList& list,
+                              hipStream_t st);
 // rows of k, v [n_seq][d] into slot `step` of kc, vc [n_seq][max_new][d]
 hipError_t launch_kv_append(const uint16_t* k, const uint16_t* v, uint16_t* kc, uint16_t* vc, int n_seq, int d,
                             int max_new, int step, hipStream_t st);
-// one query per prompt over its prefill keys kp/vp [T][H*128] and slots 0..step of kn/vn
-hipError_t launch_decode_attention(const uint16_t* q, const uint16_t* kp, const uint16_t* vp, const uint16_t* kn,
-                                   const uint16_t* vn, const int* cu, int n_seq, int T, int n_prefix, int n_heads,
-                                   int hd, int max_keys, int max_new, int step, uint16_t* o, hipStream_t st);
+// How the units (128-column tile, 64-deep stage; tile by tile, `units` of them, nst a
+// tile) of a decode product are dealt out to wgs workgroups, in runs that differ by
+// one at most: run w is units first(w) .. first(w + 1) - 1.
+struct SkinnySplit {
+    int nst, units, wgs;   // units * wgs < 2^31
+    __host__ __device__ int first(int w) const { return (int)((unsigned)(w * units) / (unsigned)wgs); }
+    __host__ __device__ int owner(int u) const { return (int)(((unsigned)(u + 1) * (unsigned)wgs - 1u) / (unsigned)units); }
+    // workgroups with a part of the tile: slots of its partial sums
+    __host__ __device__ int slots(int tile) const { return owner(tile * nst + nst - 1) - owner(tile * nst) + 1; }
+};
 
-// Decode-shaped GEMMs (few rows): K split into S chunks (S from N and K only),
-// float32 partials part[S][M][N] of A [M][K] times the weight regions b0|b1|b2
-// (each [nr][K], N = regions * nr), then reduce kernels that add the partials
-// in chunk order and finish the layer's elementwise work.
-int skinny_splits(int N, int K);
+// q, k and v of the new tokens as a product's partial sums, not yet rotated
+struct DecodeQkv {
+    const float* part;     // [slots][n_seq][3 d]; null: q, kn and vn hold them
+    SkinnySplit sp;
+    const float2* rope;
+    const int* pos;
+    int n_pos;
+};
+// one query per prompt over its prefill keys kp/vp [T][H*hd] and slots 0..step of
+// kn/vn; with qkv.part it first rotates the new token's q and k and writes its k
+// and v into slot `step`
+hipError_t launch_decode_attention(const uint16_t* q, const DecodeQkv& qkv, const uint16_t* kp, const uint16_t* vp,
+                                   uint16_t* kn, uint16_t* vn, const int* cu, int n_seq, int T, int n_prefix,
+                                   int n_heads, int hd, int max_keys, int max_new, int step, const DecodeList& list,
+                                   uint16_t* o, hipStream_t st);
+
+// Decode-shaped GEMMs (few rows): the product dealt out as skinny_split(N, K)
+// says, float32 partials part[slot][M][N] of A [M][K] times the weight regions
+// b0|b1|b2 (each [nr][K], N = regions * nr), skinny_slots(N, K) slots at most,
+// then reduce kernels that add the partials in slot order and finish the
+// layer's elementwise work.
+SkinnySplit skinny_split(int N, int K);
+int skinny_slots(int N, int K);
 bool skinny_supported(int N, int K, int nr);
 bool skinny_norm_supported(int d);
 hipError_t launch_skinny_gemm(const uint16_t* a, const uint16_t* b0, const uint16_t* b1, const uint16_t* b2,
                               int nr, int M, int N, int K, float* part, hipStream_t st);
-// x += sum of partials [S][M][d]; with h, h = bf16(RMSNorm(x) * g)
-hipError_t launch_skinny_resid_norm(const float* part, int S, int M, int d, float* x, const uint16_t* g,
+// x += sum of partials [slots][M][d]; with h, h = bf16(RMSNorm(x) * g)
+hipError_t launch_skinny_resid_norm(const float* part, SkinnySplit sp, int M, int d, float* x, const uint16_t* g,
                                     uint16_t* h, float eps, hipStream_t st);
-// q to q[M][d], k and v to slot `step` of kc, vc [M][max_new][d], RoPE at
-// pos[m] over heads of hd (128 or 64) dimensions
-hipError_t launch_skinny_qkv(const float* part, int S, int M, int d, int hd, const float2* rope, const int* pos,
-                             int n_pos, uint16_t* q, uint16_t* kc, uint16_t* vc, int max_new, int step,
-                             hipStream_t st);
 // a[M][F] = silu(gate) * up
-hipError_t launch_skinny_swiglu(const float* part, int S, int M, int F, uint16_t* a, hipStream_t st);
+hipError_t launch_skinny_swiglu(const float* part, SkinnySplit sp, int M, int F, uint16_t* a, hipStream_t st);
 
 // ---------------------------------------------------------------- f32 path
 // q|k|v = a [wq|wk|wv]^T with RoPE on q and k; x += a b^T; out = silu(a wg^T) * (a wu^T)

@@ -13,11 +13,7 @@ __global__ void rope_table_kernel(float2* __restrict__ tab, int n_pos, int half,
                                   double base) {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (long long)n_pos * half) return;
-    const int p = (int)(i / half);
-    const int j = (int)(i % half);
-    const double theta = pow(base, -2.0 * (double)j / (double)hd);
-    const double ang = (double)p * theta;
-    tab[i] = make_float2((float)cos(ang), (float)sin(ang));
+    tab[i] = rope_entry((int)(i / half), (int)(i % half), hd, base);
 }
 
 template <bool XBF16, bool GBF16, bool HBF16>

@@ -40,6 +40,13 @@ __device__ __forceinline__ T wave_sum(T v) {
     return v;
 }
 
+// (cos, sin) of RoPE's angle p * base^(-2j/hd), computed in float64
+__device__ __forceinline__ float2 rope_entry(int p, int j, int hd, double base) {
+    const double theta = pow(base, -2.0 * (double)j / (double)hd);
+    const double ang = (double)p * theta;
+    return make_float2((float)cos(ang), (float)sin(ang));
+}
+
 constexpr int kWave = 64;
 
 }  // namespace rift

@@ -1,0 +1,95 @@
+"""Decode steps at the edges of the key split (one part, several, the most; a
+prompt taken whole or in parts; a shared prefix; an empty prompt)
+and of the GEMM's row blocks and runs: outputs and the cache slot against
+float64, and bit for bit against the prompt decoded alone."""
+import numpy as np
+import pytest
+
+from tests.rift_testlib import torch_mod
+
+pytestmark = pytest.mark.gpu
+
+
+def _reference(torch, W, x, keys, values, H, hd, n_pos_of, eps=1e-6, base=10000.0):
+    """One layer in float64 for one prompt; keys and values [L][d] as cached."""
+    f = lambda t: t.double()
+    d = H * hd
+    x = f(x)
+    h = x / torch.sqrt((x * x).mean() + eps) * f(W["g_attn"])
+    q, k, v = (h @ f(W[n]).T for n in ("wq", "wk", "wv"))
+    ang = n_pos_of * base ** (-2.0 * torch.arange(hd // 2, device=x.device, dtype=torch.float64) / hd)
+    c, s = ang.cos(), ang.sin()
+
+    def rot(t):
+        t = t.view(H, hd)
+        a, b = t[:, :hd // 2], t[:, hd // 2:]
+        return torch.cat([a * c - b * s, b * c + a * s], 1).reshape(d)
+
+    q, k = rot(q), rot(k)
+    K = torch.cat([f(keys), k[None]]).view(-1, H, hd).transpose(0, 1)
+    V = torch.cat([f(values), v[None]]).view(-1, H, hd).transpose(0, 1)
+    p = torch.softmax((K @ q.view(H, hd, 1))[:, :, 0] / hd ** 0.5, dim=1)
+    x = x + f(W["wo"]) @ (p[:, :, None] * V).sum(1).reshape(d)
+    h = x / torch.sqrt((x * x).mean() + eps) * f(W["g_ffn"])
+    g = f(W["w_gate"]) @ h
+    return x + f(W["w_down"]) @ (g / (1 + torch.exp(-g)) * (f(W["w_up"]) @ h)), k, v
+
+
+CASES = [   # heads, head_dim, ffn, prompt rows, prefix rows, step
+    (8, 128, 2816, [0, 1, 63, 64, 127, 128, 129, 255, 256, 511, 512, 700, 1030], 0, 0),
+    (8, 128, 2176, [5, 300, 900] * 11, 7, 2),            # 33 rows; runs that cross tiles unevenly
+    (16, 64, 3456, [0, 127, 254, 255, 256, 700, 1100, 2100], 3, 1),
+    (8, 128, 1024, [3 + 11 * i for i in range(66)], 0, 1),      # 66 rows, parts
+    (8, 128, 1024, [2 + 5 * i for i in range(129)], 35, 3),     # 129 rows, prompts whole
+    (8, 128, 1024, [1 + i % 40 for i in range(257)], 0, 0),     # two row tiles
+    (16, 64, 1024, [1 + 17 * i for i in range(64)], 0, 0),      # whole, 64-dimensional heads
+]
+
+
+@pytest.mark.parametrize("H,hd,ffn,lens,P,step", CASES)
+def test_decode_splits(H, hd, ffn, lens, P, step):
+    import paper_2609_29029_amd as R
+    torch = torch_mod()
+    d, n, max_new = H * hd, len(lens), step + 1
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    mk = lambda *s, std=1.0, mean=0.0: torch.empty(*s, device="cuda", dtype=torch.bfloat16).normal_(mean, std, generator=g)
+    shape = dict(wq=(d, d), wk=(d, d), wv=(d, d), wo=(d, d), w_gate=(ffn, d), w_up=(ffn, d), w_down=(d, ffn))
+    W = {k: mk(*s, std=0.03) for k, s in shape.items()}
+    W["g_attn"], W["g_ffn"] = mk(d, std=0.05, mean=1.0), mk(d, std=0.05, mean=1.0)
+    cfg = R.model_cfg(d, H, hd, ffn, 1, 1e-6, 10000.0, R.RIFT_BF16)
+    cu = np.concatenate([[0], P + np.cumsum([0] + lens)]) if P else np.concatenate([[0], np.cumsum(lens)])
+    T, Lmax = int(cu[-1]), P + max(lens)
+    kv = mk(1, 2, max(T, 1), d)
+    new = mk(1, 2, n, max_new, d)
+    x = mk(n, d)
+
+    def decode(cu, n, kv, new, x, T):
+        new = new.clone()
+        new[:, :, :, step] = float("nan")   # the slot is written, never read
+        ws = torch.empty(R.rift_decode_workspace_size(cfg, n, Lmax, max_new), dtype=torch.uint8, device="cuda")
+        ws.fill_(255)
+        out = torch.empty(n, d, device="cuda")
+        for _ in range(2):                  # a second call on the same workspace gives the same
+            R.rift_decode_step(cfg, [W], x, torch.tensor(cu, dtype=torch.int32, device="cuda"), T, Lmax, kv, new, step,
+                               out, ws, n_prefix=P)
+        return out, new
+
+    out, slots = decode(cu, n, kv, new, x, T)
+    torch.cuda.synchronize()
+    own = lambda i: int(cu[i + (1 if P else 0)])
+    for i in sorted({0, 1, n // 2, n - 2, n - 1} | set(range(min(n, 13)))):
+        rows = [kv[0, j, own(i):own(i) + lens[i]] for j in (0, 1)]
+        K, V = (torch.cat([kv[0, j, :P], rows[j], new[0, j, i, :step]]) for j in (0, 1))
+        ref, k, v = _reference(torch, W, x[i], K, V, H, hd, float(P + lens[i] + step))
+        err = lambda a, b: float((a.double() - b).norm() / b.norm())
+        # bf16 roundings of h, q, k, v, o and the activation, 2^-9 each relative to its norm
+        assert err(out[i], ref) <= 1e-2, (i, lens[i], err(out[i], ref))
+        assert err(slots[0, 0, i, step], k) <= 1e-2 and err(slots[0, 1, i, step], v) <= 1e-2
+        kv1 = torch.stack([torch.cat([kv[0, j, :P], rows[j]]) for j in (0, 1)])[None].contiguous()
+        if kv1.shape[2] == 0:
+            kv1 = kv[:, :, :1].contiguous()
+        cu1 = [0, P, P + lens[i]] if P else [0, lens[i]]
+        alone, slot1 = decode(cu1, 1, kv1, new[:, :, i:i + 1].contiguous(), x[i:i + 1], kv1.shape[2])
+        assert torch.equal(alone[0], out[i]), (i, lens[i])
+        assert torch.equal(slot1[0, :, 0], slots[0, :, i])
