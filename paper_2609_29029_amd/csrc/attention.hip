@@ -10,12 +10,17 @@
 // and values from that XCD's L2 after the first fetch (HBM-side fetch per
 // layer 0.46 GB, the q, k and v bytes, against 0.79 GB when one workgroup
 // loops over a sequence's blocks and its later passes miss the L2).
-// Otherwise one workgroup per (sequence, head), looping over the sequence's
+// Other head counts, few sequences (up to 128): the same workgroups and order,
+// without a list; each finds its entry from the sequences' lengths, and those of
+// the last group's missing heads leave.  (Nine prompts of 43 to 577 rows, 20 heads
+// of 64 dimensions: 21.8 us as one workgroup per (sequence, head), 12.2 so.)
+// Many sequences: one workgroup per (sequence, head), looping over the sequence's
 // 128-query blocks, the last (longest-running) first.  Wave w owns queries
 // [32 w, 32 w + 32) of a block (sequences in packing order, so prompts packed
 // longest first start first).  Keys and values stream 64 at a time through a ring of
 // S = 2 LDS stages that LDS DMA fills a block ahead, one barrier per block,
-// and two workgroups share a CU; the last key block of a query block loads
+// and two workgroups share a CU (S = 4 is slower even where there is one for
+// each CU at most, 643 rows and 32 heads: 26.3 us against 22.3); the last key block of a query block loads
 // the first one of the next query block.  Tile rows are 256 bytes, unpadded; the
 // 16-byte chunks of row r sit at chunk ^ (r & 15) for keys and chunk ^
 // 4 (r & 3) for values, which keeps both the key-row reads and the
@@ -93,7 +98,9 @@ __device__ __forceinline__ void wait_vm(int n) {
 // 64).  With HD = 64 the tiles keep their 256-byte rows: the DMA fills only
 // the head's 8 chunks of each row, and the score and output MFMAs stop at the
 // head's dimensions (the other chunks are never read).
-template <int W, int S, int HD, bool LIST>
+enum { kLoop, kList, kScan };   // where a workgroup's query blocks come from
+
+template <int W, int S, int HD, int FROM>
 __global__ void __launch_bounds__(64 * W, W == 8 ? 1 : 2)
 attn_bf16_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                  const bf16_t* __restrict__ v, bf16_t* __restrict__ o,
@@ -101,11 +108,41 @@ attn_bf16_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                  const int2* __restrict__ list) {
     constexpr int G = W / 4;                 // query blocks per pass
     constexpr int NDMA = 32 / W;             // DMA instructions per wave per key block
+    constexpr bool LIST = FROM != kLoop;     // one query block
     static_assert(!LIST || W == 4, "the query-block kernel runs one block per pass");
     __shared__ __align__(16) unsigned char ring[S * kStageBytes];
 
     int seq, head, qb_top = -1;
-    if constexpr (LIST) {
+    if constexpr (FROM == kScan) {
+        // entry e of the list below, found by each wave: the sequence whose blocks
+        // (times groups) hold it, 64 sequences at a time
+        const int hs = (H + 7) >> 3, lane_ = threadIdx.x & 63;
+        int e = (int)(blockIdx.x >> 3);
+        seq = -1;
+        for (int base = 0; base < n_seq; base += 64) {
+            const int sq = base + lane_;
+            const int len = sq < n_seq ? cu[sq + 1] - cu[sq] : 0;
+            const int nb = len > 0 ? (len + BQ - 1) / BQ : 0;
+            int incl = nb * hs;
+#pragma unroll
+            for (int sh = 1; sh < 64; sh <<= 1) {
+                const int x = __shfl_up(incl, sh);
+                incl += lane_ >= sh ? x : 0;
+            }
+            const uint64_t past = __ballot(incl > e);
+            if (past != 0) {
+                const int l = __ffsll((unsigned long long)past) - 1;
+                const int n = __builtin_amdgcn_readlane(nb, l);
+                const int r = e - (__builtin_amdgcn_readlane(incl, l) - n * hs);
+                seq = base + l;
+                head = (r / n) * 8 + (int)(blockIdx.x & 7);
+                qb_top = n - 1 - r % n;
+                break;
+            }
+            e -= __builtin_amdgcn_readlane(incl, 63);
+        }
+        if (seq < 0 || head >= H) return;
+    } else if constexpr (FROM == kList) {
         // entry blockIdx / 8: sequence, group of 8 heads, query block; the
         // head within the group is blockIdx mod 8, the XCD the workgroup runs
         // on, so one XCD runs every query block of a (sequence, head)
@@ -450,31 +487,28 @@ hipError_t launch_attention_worklist(const int* cu, int n_seq, int n_heads, int2
 }
 
 hipError_t launch_attention_bf16(const uint16_t* q, const uint16_t* k, const uint16_t* v,
-                                 uint16_t* o, const int* cu, int n_seq, int max_seqlen,
+                                 uint16_t* o, const int* cu, int n_seq, int T, int max_seqlen,
                                  int n_heads, int hd, int n_prefix, const int2* list, int n_list,
                                  hipStream_t st) {
     if (n_seq <= 0 || max_seqlen <= 0) return hipSuccess;
     if (hd != 64 && hd != 128) return hipErrorInvalidValue;
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)hd);
-    if (list != nullptr) {
-        if (n_heads % 8 != 0 || n_list <= 0) return hipErrorInvalidValue;
-        const dim3 grid((unsigned)n_list * 8u);
-        if (hd == 128)
-            hipLaunchKernelGGL((attn_bf16_kernel<4, 2, 128, true>), grid, dim3(256), 0, st, q, k, v, o, cu, n_seq,
-                               n_heads, n_prefix, scale_log2, list);
-        else
-            hipLaunchKernelGGL((attn_bf16_kernel<4, 2, 64, true>), grid, dim3(256), 0, st, q, k, v, o, cu, n_seq,
-                               n_heads, n_prefix, scale_log2, list);
+    auto launch = [&](auto kernel, long long blocks) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, st, q, k, v, o, cu, n_seq, n_heads, n_prefix,
+                           scale_log2, list);
         return hipGetLastError();
+    };
+    // by query blocks where there is a list or few sequences to look through
+    const bool scan = list == nullptr && n_seq <= 128;
+    if (list != nullptr || scan) {
+        if (!scan && (n_heads % 8 != 0 || n_list <= 0)) return hipErrorInvalidValue;
+        const long long blocks = scan ? (long long)((n_heads + 7) / 8) * (T / BQ + n_seq) * 8 : (long long)n_list * 8;
+        if (blocks >= (1ll << 31)) return hipErrorInvalidValue;
+        if (scan) return hd == 128 ? launch(attn_bf16_kernel<4, 2, 128, kScan>, blocks) : launch(attn_bf16_kernel<4, 2, 64, kScan>, blocks);
+        return hd == 128 ? launch(attn_bf16_kernel<4, 2, 128, kList>, blocks) : launch(attn_bf16_kernel<4, 2, 64, kList>, blocks);
     }
     const long long blocks = (long long)n_seq * n_heads;
-    if (hd == 128)
-        hipLaunchKernelGGL((attn_bf16_kernel<4, 2, 128, false>), dim3((unsigned)blocks), dim3(256), 0, st, q, k, v,
-                           o, cu, n_seq, n_heads, n_prefix, scale_log2, nullptr);
-    else
-        hipLaunchKernelGGL((attn_bf16_kernel<4, 2, 64, false>), dim3((unsigned)blocks), dim3(256), 0, st, q, k, v,
-                           o, cu, n_seq, n_heads, n_prefix, scale_log2, nullptr);
-    return hipGetLastError();
+    return hd == 128 ? launch(attn_bf16_kernel<4, 2, 128, kLoop>, blocks) : launch(attn_bf16_kernel<4, 2, 64, kLoop>, blocks);
 }
 
 }  // namespace rift

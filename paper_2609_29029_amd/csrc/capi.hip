@@ -653,7 +653,7 @@ rift_status rift_prefill(const rift_model_cfg* cfg, const rift_layer_weights* la
             RIFT_TRY(mark(l, 1, 0));
             RIFT_TRY(launch_attention_bf16(static_cast<const uint16_t*>(qb), static_cast<const uint16_t*>(kb),
                                            static_cast<const uint16_t*>(vb), static_cast<uint16_t*>(h),
-                                           cu_seqlens, n_seq, max_seqlen, c.n_heads, c.head_dim, n_prefix, alist,
+                                           cu_seqlens, n_seq, T, max_seqlen, c.n_heads, c.head_dim, n_prefix, alist,
                                            n_alist, st));
             RIFT_TRY(mark(l, 1, 1));
             RIFT_TRY(mark(l, 2, 0));

@@ -183,3 +183,28 @@ def test_hd64_attention_worklist_many_sequences(R):
     i = 1024
     alone, _ = run_prefill(R, m, Wd, x[cu[i]:cu[i + 1]], np.array([0, lens[i]]), np.arange(lens[i]))
     assert np.array_equal(alone, hid[cu[i]:cu[i + 1]])
+
+
+@pytest.mark.parametrize("n_prefix", [0, 35])
+def test_hd64_attention_by_blocks_and_by_sequences(R, n_prefix):
+    """20 heads: batches of up to 128 sequences run attention by query blocks,
+    each workgroup finding its own; larger ones by sequences.  The same rows for
+    both, bit for bit: empty sequences, lengths at the edges of a query block,
+    and entries in the first and the second 64 sequences."""
+    m = model(1280, 3456)
+    rng = np.random.default_rng(128 + n_prefix)
+    Wd = [upload_layer(W, "bf16") for W in layers_for(m, 42)]
+    own = [0, 1, 127, 128, 129, 300, 0, 257] + [int(x) for x in rng.integers(0, 40, size=116)] + [130, 0, 5]
+    pre = [n_prefix] if n_prefix else []
+    lens = pre + own                                  # 127 or 128 sequences
+    x = synth.store(rng.standard_normal((sum(lens) + 20, m.d)).astype(np.float32), "bf16")
+
+    def run(lens):
+        cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        pos = np.concatenate([np.arange(l) + (n_prefix if i >= len(pre) else 0) for i, l in enumerate(lens)]).astype(np.int32)
+        return run_prefill(R, m, Wd, x[:cu[-1]], cu, pos, n_prefix=n_prefix)[0]
+
+    few = run(lens)
+    many = run(lens + [20, 0])                        # 129 or 130
+    assert np.isfinite(few).all()
+    assert np.array_equal(few, many[:len(few)])
