@@ -196,8 +196,37 @@ merge_norm_kernel(const void* __restrict__ tokens, int n_v, int d, const int* __
     if (rho >= 0) {
         const int t = tgt[(size_t)rho * n_v + j];
         const size_t base = ((size_t)kept[rho] * n_v + t) * (size_t)d + 8 * q;
-#pragma unroll 8
-        for (int s = 0; s < d / 32; ++s) {
+        // the launch waits for one wave's chain of loads: 32 of them in flight (d =
+        // 4,096: 18.5 us with 8, 11.4 so)
+        constexpr int NF = BF16 ? 32 : 16;
+        constexpr int EB = BF16 ? 2 : 4, W = 8 * EB / 16;   // 16-byte words of a granule
+        const char* p = static_cast<const char*>(tokens) + base * EB;
+        int s = 0;
+        for (; s + NF <= d / 32; s += NF) {
+            u32x4_t w[NF][W];
+#pragma unroll
+            for (int u = 0; u < NF; ++u)
+#pragma unroll
+                for (int i = 0; i < W; ++i) w[u][i] = *reinterpret_cast<const u32x4_t*>(p + (size_t)(s + u) * 32 * EB + 16 * i);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < NF; ++u)
+#pragma unroll
+                for (int i = 0; i < W; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const uint32_t b = w[u][i][e];
+                        if constexpr (BF16) {
+                            const double lo = (double)bf16_lo(b), hi = (double)bf16_hi(b);
+                            acc = fma(lo, lo, acc);
+                            acc = fma(hi, hi, acc);
+                        } else {
+                            const double x = (double)__uint_as_float(b);
+                            acc = fma(x, x, acc);
+                        }
+                    }
+        }
+        for (; s < d / 32; ++s) {
             double v[8];
             load8<BF16>(tokens, base + 32 * s, v);
 #pragma unroll
@@ -240,9 +269,10 @@ merge_norm_kernel(const void* __restrict__ tokens, int n_v, int d, const int* __
 // tokens a wave leave too few waves in flight to stream the tokens), targets in
 // chunks of 64; the partial scores are added through LDS.  Workgroup b runs on
 // XCD b mod 8 and tiles go to XCDs whole, so a tile's target rows stay in one L2.
-// Measured on those 100 tiles (360 MB of remaining tokens): 118 us, 3.1 TB/s (108
-// us without the cdot rounds); the waves taking a row's pieces in turn instead of
-// quarters 124-140 us.
+// Measured on those 100 tiles (360 MB of remaining tokens): 114 us, 3.2 TB/s (118
+// with 256 bytes of a token's row in flight instead of 512; about 10 of them the
+// cdot rounds); the waves taking a row's pieces in turn instead of quarters 124-140
+// us, the next piece's tokens loaded ahead 123.
 constexpr int kAT = 16;     // tokens per workgroup
 constexpr int kJC = 64;     // targets per chunk: four 16-row MFMA blocks
 constexpr int kSeg = 8;     // 32-element MFMA steps per float32 partial sum
@@ -293,28 +323,35 @@ merge_assign_mfma_kernel(const bf16_t* __restrict__ tokens, int n_v, int d, cons
         f32x4_t acc[4] = {zero, zero, zero, zero}, self = zero;
         auto pass = [&](auto kNB) __attribute__((always_inline)) {
             constexpr int NB = decltype(kNB)::value;
-            constexpr int U = NB > 2 ? 2 : NB > 1 ? 4 : kSeg;   // loads in flight, within 128 registers
+            // steps of the tokens and of the targets in flight, within 128 registers
+            constexpr int U = NB > 2 ? 4 : kSeg, UY = NB > 2 ? 2 : NB > 1 ? 4 : kSeg;
             for (int s = s0; s < s1; s += U) {
                 f32x4_t seg[NB];
 #pragma unroll
                 for (int b = 0; b < NB; ++b) seg[b] = zero;
                 if (s + U <= s1) {
-                    u32x4_t x[U], y[NB][U];
+                    u32x4_t x[U];
 #pragma unroll
                     for (int u = 0; u < U; ++u) x[u] = *reinterpret_cast<const u32x4_t*>(xrow + 32 * (s + u));
 #pragma unroll
-                    for (int b = 0; b < NB; ++b)
-#pragma unroll
-                        for (int u = 0; u < U; ++u)
-                            y[b][u] = *reinterpret_cast<const u32x4_t*>(yrow[b] + 32 * (s + u));
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const bf16x8_t xf = __builtin_bit_cast(bf16x8_t, x[u]);
-                        if (jc == 0) self = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf, xf, self, 0, 0, 0);
+                    for (int u0 = 0; u0 < U; u0 += UY) {
+                        u32x4_t y[NB][UY];
 #pragma unroll
                         for (int b = 0; b < NB; ++b)
-                            seg[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, y[b][u]), xf,
-                                                                             seg[b], 0, 0, 0);
+#pragma unroll
+                            for (int u = 0; u < UY; ++u)
+                                y[b][u] = *reinterpret_cast<const u32x4_t*>(yrow[b] + 32 * (s + u0 + u));
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int u = 0; u < UY; ++u) {
+                            const bf16x8_t xf = __builtin_bit_cast(bf16x8_t, x[u0 + u]);
+                            if (jc == 0) self = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf, xf, self, 0, 0, 0);
+#pragma unroll
+                            for (int b = 0; b < NB; ++b)
+                                seg[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, y[b][u]), xf,
+                                                                                 seg[b], 0, 0, 0);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
                     }
                 } else {   // the quarter's last, shorter piece
                     for (int v = s; v < s1; ++v) {
