@@ -592,15 +592,17 @@ rift_status rift_prefill(const rift_model_cfg* cfg, const rift_layer_weights* la
         }
         return RIFT_OK;
     }
-    RIFT_TRY(launch_rope_table(rope, max_seqlen, c.head_dim, c.rope_base, st));
     // attention work list (one entry per sequence, group of 8 heads and
-    // 128-query block), built once for every layer
+    // 128-query block), built once for every layer, with the RoPE table
     int2* alist = nullptr;
     int n_alist = 0;
     if (attention_list_capacity(c, T) > 0) {
         alist = reinterpret_cast<int2*>(ws + L.alist);
         n_alist = attention_worklist_entries(T, n_seq, c.n_heads);
-        RIFT_TRY(launch_attention_worklist(cu_seqlens, n_seq, c.n_heads, alist, n_alist, st));
+        RIFT_TRY(launch_attention_worklist(cu_seqlens, n_seq, c.n_heads, alist, n_alist, rope, max_seqlen, c.head_dim,
+                                           c.rope_base, st));
+    } else {
+        RIFT_TRY(launch_rope_table(rope, max_seqlen, c.head_dim, c.rope_base, st));
     }
     // benchmark hook: event pair around stage g of layer l (NULL entries skipped)
     auto mark = [&](int l, int g, int end) -> hipError_t {

@@ -92,8 +92,9 @@ hipError_t launch_attention_bf16(const uint16_t* q, const uint16_t* k, const uin
 // entry per sequence, group of 8 heads and query block; unused entries up to
 // n_list are marked empty); n_list >= attention_worklist_entries(T, n_seq, H).
 int attention_worklist_entries(int T, int n_seq, int n_heads);
-hipError_t launch_attention_worklist(const int* cu, int n_seq, int n_heads, int2* list, int n_list,
-                                     hipStream_t st);
+// Also fills the RoPE table, as launch_rope_table.
+hipError_t launch_attention_worklist(const int* cu, int n_seq, int n_heads, int2* list, int n_list, float2* rope,
+                                     int n_pos, int hd, double rope_base, hipStream_t st);
 
 // ---------------------------------------------------------------- decode (bf16)
 // What a decode step needs before its layers: pos[i] = (keys of prompt i) - 1, the
