@@ -428,13 +428,24 @@ int decode_chunk(int hd) { return hd == 128 ? kChunk<128> : kChunk<64>; }
 // A workgroup takes a prompt whole where that gives each CU four (100 prompts, 32
 // heads: 67 us against 74 in parts of 128 keys; one prompt in parts 9, the 32 workgroups of one
 // taken whole read its keys on an eighth of the chip).
-static bool whole_prompts(int64_t n_seq, int n_heads) { return n_seq * n_heads >= 1024; }
-
-int64_t decode_entries(int64_t n_seq, int64_t max_keys, int n_heads, int hd) {
+constexpr int64_t kWholeItems = 1024;
+static bool whole_prompts(int64_t n_seq, int n_heads) { return n_seq * n_heads >= kWholeItems; }
+static int64_t entries_of(int64_t n_seq, int64_t max_keys, int n_heads, int hd) {
     return whole_prompts(n_seq, n_heads) ? n_seq : n_seq * key_parts((int)max_keys, decode_chunk(hd));
 }
+
+// What a workspace holds is for n_seq prompts or any fewer, so that it never
+// shrinks with n_seq: fewer prompts are taken in parts, and need more.
+static int64_t most_in_parts(int64_t n_seq, int n_heads) {
+    const int64_t most = (kWholeItems - 1) / n_heads;
+    return n_seq < most ? n_seq : most;
+}
+int64_t decode_entries(int64_t n_seq, int64_t max_keys, int n_heads, int hd) {
+    const int64_t split = most_in_parts(n_seq, n_heads) * key_parts((int)max_keys, decode_chunk(hd));
+    return split > n_seq ? split : n_seq;
+}
 int64_t decode_part_floats(int64_t n_seq, int64_t max_keys, int n_heads, int hd) {
-    return whole_prompts(n_seq, n_heads) ? 0 : decode_entries(n_seq, max_keys, n_heads, hd) * n_heads * 4 * (hd + 2);
+    return most_in_parts(n_seq, n_heads) * key_parts((int)max_keys, decode_chunk(hd)) * n_heads * 4 * (hd + 2);
 }
 
 hipError_t launch_decode_prep(const int* cu, int n_seq, int n_heads, int hd, int T, int n_prefix, int step,
@@ -481,7 +492,7 @@ hipError_t launch_decode_attention(const uint16_t* q, const DecodeQkv& qkv, cons
     p.list = list;
     p.o = o;
     p.whole = whole_prompts(n_seq, n_heads) ? 1 : 0;
-    int64_t wgs = decode_entries(n_seq, max_keys, n_heads, hd) * n_heads;   // those past the list's end leave
+    int64_t wgs = entries_of(n_seq, max_keys, n_heads, hd) * n_heads;   // those past the list's end leave
     if (wgs > (1 << 20)) wgs = 1 << 20;
     const dim3 grid((unsigned)wgs);
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, p, list.n, list.entry); };

@@ -100,8 +100,8 @@ hipError_t launch_attention_worklist(const int* cu, int n_seq, int n_heads, int2
 // What a decode step needs before its layers: pos[i] = (keys of prompt i) - 1, the
 // position of its new token; the RoPE table (as launch_rope_table); the
 // attention's work list, one entry per workgroup and head; and n_seq * n_heads
-// arrival counters cleared.  List and partial results have decode_entries and
-// decode_part_floats elements at most.
+// arrival counters cleared.  List and partial results have at most decode_entries
+// and decode_part_floats elements for n_seq prompts or any fewer.
 int decode_chunk(int hd);
 int64_t decode_entries(int64_t n_seq, int64_t max_keys, int n_heads, int hd);
 int64_t decode_part_floats(int64_t n_seq, int64_t max_keys, int n_heads, int hd);

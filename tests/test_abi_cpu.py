@@ -306,3 +306,18 @@ def test_decode_validation(R):
     # shared prefix longer than the prefill batch, or negative
     assert d(ctypes.byref(cfg), lw, FAKE, FAKE, 4, 100, 643, 101, FAKE, FAKE, 8, 0, FAKE, FAKE, ws, None) == 2
     assert d(ctypes.byref(cfg), lw, FAKE, FAKE, 4, 100, 643, -1, FAKE, FAKE, 8, 0, FAKE, FAKE, ws, None) == 2
+
+
+@pytest.mark.parametrize("d,heads,hd,ffn", [(4096, 32, 128, 11008), (1024, 16, 64, 2816), (1280, 20, 64, 3456),
+                                            (256, 2, 128, 512)])
+def test_decode_workspace_does_not_shrink_with_more_prompts(R, d, heads, hd, ffn):
+    """A serving loop allocates for its most prompts and goes on with fewer as
+    prompts finish, or with shorter ones: what the larger call was given has to
+    do for the smaller one."""
+    cfg = R.model_cfg(d, heads, hd, ffn, 2, 1e-6, 10000.0, R.RIFT_BF16)
+    for L in (1, 100, 128, 129, 692, 2000, 16000):
+        sizes = [R.rift_decode_workspace_size(cfg, n, L, 8) for n in range(0, 600)]
+        assert all(a <= b for a, b in zip(sizes, sizes[1:])), (L, [n for n in range(599) if sizes[n] > sizes[n + 1]])
+    for n in (1, 7, 31, 32, 100, 512):
+        sizes = [R.rift_decode_workspace_size(cfg, n, L, 8) for L in range(0, 3000, 7)]
+        assert all(a <= b for a, b in zip(sizes, sizes[1:])), n
