@@ -325,11 +325,40 @@ attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const 
         l = fmaf(l, alpha, sum);
         m = mn;
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
+        for (int s = 0; s < NS; ++s)
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[s][e] *= alpha;
+        // A key that some query of the wave must not see has probability 0 for it,
+        // and 0 times a value that is not finite is NaN: then key by key, and only
+        // for the queries that see the key.
+        bool hidden = false;
+        if (k0 + 15 > pre + i0) {   // wave-uniform: one or two blocks of a wave
+            float z = 0.f;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[i][s], sc[i], acc[s], 0, 0, 0);
+            for (int s = 0; s < NS; ++s)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) z = fmaf(vc[i][s], 0.f, z);
+            hidden = __any(z != z);
+        }
+        if (!hidden) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    acc[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[i][s], sc[i], acc[s], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                for (int kg = 0; kg < 4; ++kg) {
+                    const bool sees = k0 + 4 * kg + i <= pre + qi;
+                    const float pr = g == kg && sees ? sc[i] : 0.f;
+#pragma unroll
+                    for (int s = 0; s < NS; ++s) {
+                        const f32x4_t with = __builtin_amdgcn_mfma_f32_16x16x4f32(g == kg ? vc[i][s] : 0.f, pr, acc[s], 0, 0, 0);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[s][e] = sees ? with[e] : acc[s][e];
+                    }
+                }
         }
     }
     if (i0 + r < L) {

@@ -60,3 +60,50 @@ def test_f32_tiles_against_oracle(d, hd, ffn, lens, checked):
     whole = run([7 + lens[1]], np.concatenate([x[:7], x[cu[1]:cu[2]]]))
     split = run([7, lens[1]], np.concatenate([x[:7], x[cu[1]:cu[2]]]), n_prefix=7)
     assert np.array_equal(whole[0], split[0]) and np.array_equal(whole[1], split[1])
+
+
+def prefill_f32(lens, xs, W, cfg, n_prefix=0, positions=None, max_seqlen=None):
+    import paper_2609_29029_amd as R
+    torch = torch_mod()
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    pos = np.concatenate([np.arange(n) + (n_prefix if i else 0) for i, n in enumerate(lens)])
+    pos = (pos if positions is None else positions).astype(np.int32)
+    T, L = int(cu[-1]), max_seqlen or max(lens) + n_prefix
+    ws = torch.empty(R.rift_prefill_workspace_size(cfg, T, L), dtype=torch.uint8, device="cuda")
+    ws.fill_(255)
+    hid = torch.empty(T, xs.shape[1], dtype=torch.float32, device="cuda")
+    R.rift_prefill(cfg, [W], upload(xs, "f32"), torch.from_numpy(cu).cuda(), torch.from_numpy(pos).cuda(), len(lens), L,
+                   hid, ws, n_prefix=n_prefix)
+    torch.cuda.synchronize()
+    return hid.cpu().numpy(), cu
+
+
+def small_model(d, hd, ffn):
+    import paper_2609_29029_amd as R
+    m = synth.ModelShape(d=d, n_heads=d // hd, head_dim=hd, ffn=ffn, n_layers=1)
+    W = synth.make_layer(dataclasses.replace(synth.get("tiny"), model=m, cid=90 + hd), 0)
+    cfg = R.model_cfg(d, d // hd, hd, ffn, 1, m.rms_eps, m.rope_base, R.RIFT_F32)
+    return {k: upload(v, "f32") for k, v in W.items()}, cfg
+
+
+@pytest.mark.parametrize("hd,pre", [(64, 0), (128, 0), (64, 5), (128, 19)])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_f32_rows_before_a_non_finite_one_do_not_see_it(hd, pre, value):
+    """Causal attention: a token that is not finite makes itself and the rows
+    after it in its sequence not finite, and no other row, wherever in a key
+    block it stands."""
+    W, cfg = small_model(256, hd, 48)
+    rng = np.random.default_rng(hd + pre)
+    x = rng.standard_normal((pre + 3 * 37, 256)).astype(np.float32)
+    lens = ([pre] if pre else []) + [37, 37, 37]
+    good, cu = prefill_f32(lens, x, W, cfg, pre)
+    first = 1 if pre else 0
+    for j in (0, 1, 14, 15, 16, 17, 33, 36):
+        bad = x.copy()
+        row = cu[first + 1] + j                    # of the middle prompt
+        bad[row, 3] = value
+        got, _ = prefill_f32(lens, bad, W, cfg, pre)
+        after = np.zeros(len(x), bool)
+        after[row:cu[first + 2]] = True
+        assert np.array_equal(got[~after], good[~after]), j
+        assert np.isnan(got[after]).all(axis=1).all(), j
