@@ -249,126 +249,126 @@ hipError_t launch_gemm_f32(const GemmF32Params& p, hipStream_t st) {
 // sequence's first logical key (shared prefix rows first), so a row's result
 // does not depend on the packing.
 template <int HD>
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(64, HD == 64 ? 3 : 2)
 attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
                 float* __restrict__ o, const int* __restrict__ cu, int H, int n_prefix, float scale) {
     constexpr int NS = HD / 16;
     const int seq = blockIdx.x / H, head = blockIdx.x % H;
     const int s0 = cu[seq];
     const int L = cu[seq + 1] - s0;
-    const int i0 = blockIdx.y * 16;
-    if (i0 >= L) return;
     const int pre = seq > 0 ? n_prefix : 0;
     const int lane = threadIdx.x, r = lane & 15, g = lane >> 4;
     const int ld = H * HD;
-    const int qi = i0 + r < L ? i0 + r : L - 1;      // this lane's query
-    const int last = pre + (i0 + 15 < L ? i0 + 15 : L - 1);   // logical position of the wave's last query
     const size_t hoff = (size_t)head * HD;
-    auto row = [&](int key) -> size_t {              // logical key, clamped to the wave's last
-        const int j = key < last ? key : last;
-        return (size_t)(j < pre ? j : s0 + j - pre) * ld + hoff;
-    };
-    f32x4_t qf[NS];
+    for (int i0 = blockIdx.y * 16; i0 < L; i0 += gridDim.y * 16) {
+        const int qi = i0 + r < L ? i0 + r : L - 1;      // this lane's query
+        const int last = pre + (i0 + 15 < L ? i0 + 15 : L - 1);   // logical position of the wave's last query
+        auto row = [&](int key) -> size_t {              // logical key, clamped to the wave's last
+            const int j = key < last ? key : last;
+            return (size_t)(j < pre ? j : s0 + j - pre) * ld + hoff;
+        };
+        f32x4_t qf[NS];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) qf[s] = load4(q + (size_t)(s0 + qi) * ld + hoff + 16 * s + 4 * g);
-    f32x4_t acc[NS];
+        for (int s = 0; s < NS; ++s) qf[s] = load4(q + (size_t)(s0 + qi) * ld + hoff + 16 * s + 4 * g);
+        f32x4_t acc[NS];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) acc[s] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    float m = -INFINITY, l = 0.f;
-    f32x4_t kf[NS];
-    float vf[4][NS];
-    auto load = [&](int k0) __attribute__((always_inline)) {
-        const size_t kr = row(k0 + r);
+        for (int s = 0; s < NS; ++s) acc[s] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        float m = -INFINITY, l = 0.f;
+        f32x4_t kf[NS];
+        float vf[4][NS];
+        auto load = [&](int k0) __attribute__((always_inline)) {
+            const size_t kr = row(k0 + r);
 #pragma unroll
-        for (int s = 0; s < NS; ++s) kf[s] = load4(k + kr + 16 * s + 4 * g);
+            for (int s = 0; s < NS; ++s) kf[s] = load4(k + kr + 16 * s + 4 * g);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const size_t vr = row(k0 + 4 * g + i);
+            for (int i = 0; i < 4; ++i) {
+                const size_t vr = row(k0 + 4 * g + i);
 #pragma unroll
-            for (int s = 0; s < NS; ++s) vf[i][s] = v[vr + 16 * s + r];
-        }
-    };
-    load(0);
-    for (int k0 = 0; k0 <= last; k0 += 16) {
-        f32x4_t kc[NS];
-        float vc[4][NS];
+                for (int s = 0; s < NS; ++s) vf[i][s] = v[vr + 16 * s + r];
+            }
+        };
+        load(0);
+        for (int k0 = 0; k0 <= last; k0 += 16) {
+            f32x4_t kc[NS];
+            float vc[4][NS];
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            kc[s] = kf[s];
+            for (int s = 0; s < NS; ++s) {
+                kc[s] = kf[s];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) vc[i][s] = vf[i][s];
-        }
-        if (k0 + 16 <= last) load(k0 + 16);
-        f32x4_t sc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < NS; ++s)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) sc = __builtin_amdgcn_mfma_f32_16x16x4f32(kc[s][i], qf[s][i], sc, 0, 0, 0);
-        float bm = -INFINITY;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            sc[i] = k0 + 4 * g + i <= pre + qi ? sc[i] * scale : -INFINITY;
-            bm = fmaxf(bm, sc[i]);
-        }
-        bm = fmaxf(bm, __shfl_xor(bm, 16));
-        bm = fmaxf(bm, __shfl_xor(bm, 32));
-        const float mn = fmaxf(m, bm);      // finite: logical key 0 is in the first block
-        const float alpha = expf(m - mn);
-        float sum = 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            sc[i] = expf(sc[i] - mn);
-            sum += sc[i];
-        }
-        sum += __shfl_xor(sum, 16);
-        sum += __shfl_xor(sum, 32);
-        l = fmaf(l, alpha, sum);
-        m = mn;
-#pragma unroll
-        for (int s = 0; s < NS; ++s)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[s][e] *= alpha;
-        // A key that some query of the wave must not see has probability 0 for it,
-        // and 0 times a value that is not finite is NaN: then key by key, and only
-        // for the queries that see the key.
-        bool hidden = false;
-        if (k0 + 15 > pre + i0) {   // wave-uniform: one or two blocks of a wave
-            float z = 0.f;
+                for (int i = 0; i < 4; ++i) vc[i][s] = vf[i][s];
+            }
+            if (k0 + 16 <= last) load(k0 + 16);
+            f32x4_t sc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int s = 0; s < NS; ++s)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) z = fmaf(vc[i][s], 0.f, z);
-            hidden = __any(z != z);
-        }
-        if (!hidden) {
+                for (int i = 0; i < 4; ++i) sc = __builtin_amdgcn_mfma_f32_16x16x4f32(kc[s][i], qf[s][i], sc, 0, 0, 0);
+            float bm = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                sc[i] = k0 + 4 * g + i <= pre + qi ? sc[i] * scale : -INFINITY;
+                bm = fmaxf(bm, sc[i]);
+            }
+            bm = fmaxf(bm, __shfl_xor(bm, 16));
+            bm = fmaxf(bm, __shfl_xor(bm, 32));
+            const float mn = fmaxf(m, bm);      // finite: logical key 0 is in the first block
+            const float alpha = expf(m - mn);
+            float sum = 0.f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                sc[i] = expf(sc[i] - mn);
+                sum += sc[i];
+            }
+            sum += __shfl_xor(sum, 16);
+            sum += __shfl_xor(sum, 32);
+            l = fmaf(l, alpha, sum);
+            m = mn;
 #pragma unroll
             for (int s = 0; s < NS; ++s)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[s][e] *= alpha;
+            // A key that some query of the wave must not see has probability 0 for it,
+            // and 0 times a value that is not finite is NaN: then key by key, and only
+            // for the queries that see the key.
+            bool hidden = false;
+            if (k0 + 15 > pre + i0) {   // wave-uniform: one or two blocks of a wave
+                float z = 0.f;
+#pragma unroll
+                for (int s = 0; s < NS; ++s)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) z = fmaf(vc[i][s], 0.f, z);
+                hidden = __any(z != z);
+            }
+            if (!hidden) {
+#pragma unroll
+                for (int s = 0; s < NS; ++s)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        acc[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[i][s], sc[i], acc[s], 0, 0, 0);
+            } else {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    acc[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[i][s], sc[i], acc[s], 0, 0, 0);
-        } else {
+                    for (int kg = 0; kg < 4; ++kg) {
+                        const bool sees = k0 + 4 * kg + i <= pre + qi;
+                        const float pr = g == kg && sees ? sc[i] : 0.f;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                for (int kg = 0; kg < 4; ++kg) {
-                    const bool sees = k0 + 4 * kg + i <= pre + qi;
-                    const float pr = g == kg && sees ? sc[i] : 0.f;
+                        for (int s = 0; s < NS; ++s) {
+                            const f32x4_t with = __builtin_amdgcn_mfma_f32_16x16x4f32(g == kg ? vc[i][s] : 0.f, pr, acc[s], 0, 0, 0);
 #pragma unroll
-                    for (int s = 0; s < NS; ++s) {
-                        const f32x4_t with = __builtin_amdgcn_mfma_f32_16x16x4f32(g == kg ? vc[i][s] : 0.f, pr, acc[s], 0, 0, 0);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) acc[s][e] = sees ? with[e] : acc[s][e];
+                            for (int e = 0; e < 4; ++e) acc[s][e] = sees ? with[e] : acc[s][e];
+                        }
                     }
-                }
+            }
         }
-    }
-    if (i0 + r < L) {
-        float* out = o + (size_t)(s0 + qi) * ld + hoff + 4 * g;
+        if (i0 + r < L) {
+            float* out = o + (size_t)(s0 + qi) * ld + hoff + 4 * g;
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            f32x4_t y;
+            for (int s = 0; s < NS; ++s) {
+                f32x4_t y;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) y[e] = acc[s][e] / l;
-            *reinterpret_cast<f32x4_t*>(out + 16 * s) = y;   // dimensions 16 s + 4 g .. + 3
+                for (int e = 0; e < 4; ++e) y[e] = acc[s][e] / l;
+                *reinterpret_cast<f32x4_t*>(out + 16 * s) = y;   // dimensions 16 s + 4 g .. + 3
+            }
         }
     }
 }

@@ -107,3 +107,17 @@ def test_f32_rows_before_a_non_finite_one_do_not_see_it(hd, pre, value):
         after[row:cu[first + 2]] = True
         assert np.array_equal(got[~after], good[~after]), j
         assert np.isnan(got[after]).all(axis=1).all(), j
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+def test_f32_attends_in_sequences_longer_than_declared(hd):
+    """max_seqlen bounds the positions (the RoPE table); rows of a sequence past
+    it are attended all the same, as in the bfloat16 path."""
+    W, cfg = small_model(256, hd, 48)
+    rng = np.random.default_rng(hd)
+    lens = [20, 75, 33]
+    x = rng.standard_normal((sum(lens), 256)).astype(np.float32)
+    positions = np.concatenate([np.arange(n) for n in lens]) % 17
+    whole, _ = prefill_f32(lens, x, W, cfg, positions=positions)
+    short, _ = prefill_f32(lens, x, W, cfg, positions=positions, max_seqlen=17)
+    assert np.array_equal(whole, short)
