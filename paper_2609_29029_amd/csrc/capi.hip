@@ -825,8 +825,10 @@ rift_status rift_decode_step(const rift_model_cfg* cfg, const rift_layer_weights
         float* part = reinterpret_cast<float*>(ws + L.part);
         const int F = c.ffn;
         const SkinnySplit s_o = skinny_split(d, d), s_gu = skinny_split(2 * F, d), s_dn = skinny_split(d, F);
-        qkv.part = part;
-        qkv.sp = skinny_split(3 * d, d);
+        const SkinnySplit s_qkv = skinny_split(3 * d, d);
+        const bool many = decode_many(n_seq, c.n_heads, c.head_dim, n_pos);
+        qkv.part = many ? nullptr : part;
+        qkv.sp = s_qkv;
         qkv.rope = rope;
         qkv.pos = pos;
         qkv.n_pos = n_pos;
@@ -837,7 +839,10 @@ rift_status rift_decode_step(const rift_model_cfg* cfg, const rift_layer_weights
             uint16_t* vn = static_cast<uint16_t*>(kv_new) + (size_t)(2 * l + 1) * nd;
             RIFT_TRY(launch_skinny_gemm(h, static_cast<const uint16_t*>(w.wq), static_cast<const uint16_t*>(w.wk),
                                         static_cast<const uint16_t*>(w.wv), d, n_seq, 3 * d, d, part, st));
-            RIFT_TRY(launch_decode_attention(nullptr, qkv, static_cast<const uint16_t*>(kv_cache) + (size_t)(2 * l) * td,
+            if (many) {
+                RIFT_TRY(launch_skinny_qkv(part, s_qkv, n_seq, d, c.head_dim, rope, pos, n_pos, qb, kn, vn, max_new, step, st));
+            }
+            RIFT_TRY(launch_decode_attention(qb, qkv, static_cast<const uint16_t*>(kv_cache) + (size_t)(2 * l) * td,
                                              static_cast<const uint16_t*>(kv_cache) + (size_t)(2 * l + 1) * td, kn,
                                              vn, cu_p, n_seq, total_tokens, n_prefix, c.n_heads, c.head_dim,
                                              n_pos, max_new, step, list, h, st));

@@ -25,14 +25,18 @@
 //                  After the split-K q, k, v product the kernel also adds its
 //                  partial sums and rotates its head of q and k while the
 //                  keys arrive.
+//   decode_attn_many   the same streams in two passes, for many prompts; the q, k, v
+//                  partial sums are then added by a kernel of their own.
 //
 // Bound by a round's latency where prompts are few, by the cache's bytes where
 // they are many.  One prompt of 647 keys, 32 heads: 24 us + 4.7 for the q, k, v
-// reduction -> 9 (two passes over the keys by one workgroup a head before); 100 of
-// 100 to 650 keys (364 MB): 57 + 5.3 -> 67 (5.4 TB/s), and with each prompt split as
-// if alone 74.
+// reduction -> 9 (two passes over the keys by one workgroup a head before).
 #include "launch.h"
 #include "rift_common.h"
+
+// Two kernels compute the same streams: multiply-adds are fused where fmaf says
+// so and nowhere else, so that their results agree bit for bit.
+#pragma clang fp contract(off)
 
 namespace rift {
 
@@ -163,6 +167,76 @@ __device__ __forceinline__ float exp2_ref(float s, float m) {
     return __builtin_amdgcn_exp2f(s - (m == -INFINITY ? 0.f : m));
 }
 
+// Sums of acc (columns 8 c .. 8 c + 7) and l over the row groups of a wave, as
+// pairs of neighbouring groups first: swaps of registers between lane halves
+// leave each lane two columns, from 8 c + row_columns() on, and every lane l.
+template <int G>
+__device__ __forceinline__ void group_reduce(float (&acc)[8], float& l, float (&v)[2]) {
+    if constexpr (G == 8) {   // the two groups of a 16-lane row: row_ror:8
+        auto add8 = [](float x) {
+            return x + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x128, 0xf, 0xf, false));
+        };
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] = add8(acc[i]);
+        l = add8(l);
+    }
+    auto rows = [](float a, float b) {     // a of rows 0 + 1 | b of rows 0 + 1 | a of 2 + 3 | b of 2 + 3
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    };
+    auto halves = [](float a, float b) {   // a of both halves | b of both halves
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    };
+    float x[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = rows(acc[i], acc[i + 4]);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) v[i] = halves(x[i], x[i + 2]);
+    l = rows(l, l);
+    l = halves(l, l);
+}
+
+// A stream's end: its sums into st [HD + 2].
+template <int HD>
+__device__ __forceinline__ void end_stream(float (&acc)[8], float l, float m, int lane, float* st) {
+    constexpr int G = HD / 8;
+    float v[2];
+    group_reduce<G>(acc, l, v);
+    const int row = lane >> 4;
+    if (G == 16 || (lane & 8) == 0)
+        *reinterpret_cast<float2*>(st + 8 * (lane % G) + 4 * (row & 1) + 2 * (row >> 1)) = make_float2(v[0], v[1]);
+    if (lane == 0) *reinterpret_cast<float2*>(st + HD) = make_float2(m, l);
+}
+
+// The streams of one (prompt, head) joined in their order, a part's four at a
+// time: column tid of the output.
+template <int HD>
+__device__ __forceinline__ bf16_t join_streams(const float* streams, int n_parts, int tid) {
+    constexpr int ST = HD + 2;
+    float mx = -INFINITY, L = 0.f, A = 0.f;
+    for (int q = 0; q < n_parts; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) mx = fmaxf(mx, streams[(4 * q + i) * ST + HD]);
+    for (int q = 0; q < n_parts; ++q) {
+        float m[4], l[4], a[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float* st = streams + (4 * q + i) * ST;
+            m[i] = st[HD];
+            l[i] = st[HD + 1];
+            a[i] = st[tid];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float f = exp2_ref(m[i], mx);
+            L = fmaf(f, l[i], L);
+            A = fmaf(f, a[i], A);
+        }
+    }
+    return f32_to_bf16(A * (1.0f / L));
+}
+
 // The work list is read through pointers of its own, so that its uniform loads
 // are scalar ones.
 template <int HD, bool FUSED>
@@ -175,7 +249,7 @@ decode_attn_kernel(DecodeAttnParams p, const int* __restrict__ n_entries, const 
     constexpr int ST = HD + 2;            // a stream's weighted values, max and sum
     __shared__ __align__(16) float qs[HD];
     __shared__ __align__(16) bf16_t kvs[2][HD];   // the new token's key and value
-    __shared__ float streams[4 * kMaxParts][ST];
+    __shared__ __align__(16) float streams[4 * kMaxParts][ST];
     __shared__ int last;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -255,8 +329,9 @@ decode_attn_kernel(DecodeAttnParams p, const int* __restrict__ n_entries, const 
                 }
                 float y1 = x1, y2 = x2;
                 if (wave < 2) {
-                    y1 = x1 * cs.x - x2 * cs.y;
-                    y2 = x2 * cs.x + x1 * cs.y;
+                    const float2 y = rotate_pair(x1, x2, cs);
+                    y1 = y.x;
+                    y2 = y.y;
                 }
                 const bf16_t o1 = f32_to_bf16(y1), o2 = f32_to_bf16(y2);
                 if (wave == 0) {
@@ -341,22 +416,8 @@ decode_attn_kernel(DecodeAttnParams p, const int* __restrict__ n_entries, const 
                 }
             }
             load_v(next + lane / G);
-            if (next_part != part) {   // the stream's end: its row groups in fixed order
-#pragma unroll
-                for (int s = G; s < 64; s <<= 1) {
-                    l += __shfl_xor(l, s);
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) acc[i] += __shfl_xor(acc[i], s);
-                }
-                float* st = streams[4 * (part - part0) + wave];
-                if (lane < G) {
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) st[8 * c + i] = acc[i];
-                    if (lane == 0) {
-                        st[HD] = m;
-                        st[HD + 1] = l;
-                    }
-                }
+            if (next_part != part) {   // the stream's end
+                end_stream<HD>(acc, l, m, lane, streams[4 * (part - part0) + wave]);
                 m = -INFINITY;
                 l = 0.f;
 #pragma unroll
@@ -367,18 +428,9 @@ decode_attn_kernel(DecodeAttnParams p, const int* __restrict__ n_entries, const 
             r0 = next;
         }
         __syncthreads();
-        const int n_streams = 4 * n_parts;
         auto join = [&]() __attribute__((always_inline)) {
-            if (tid < HD) {
-                float mx = -INFINITY, L = 0.f, A = 0.f;
-                for (int i = 0; i < n_streams; ++i) mx = fmaxf(mx, streams[i][HD]);
-                for (int i = 0; i < n_streams; ++i) {
-                    const float f = exp2_ref(streams[i][HD], mx);
-                    L = fmaf(f, streams[i][HD + 1], L);
-                    A = fmaf(f, streams[i][tid], A);
-                }
-                p.o[(size_t)seq * ld + (size_t)head * HD + tid] = f32_to_bf16(A * (1.0f / L));
-            }
+            if (tid < HD)
+                p.o[(size_t)seq * ld + (size_t)head * HD + tid] = join_streams<HD>(streams[0], n_parts, tid);
         };
         if (part1 - part0 == n_parts) {
             join();
@@ -421,6 +473,130 @@ decode_attn_kernel(DecodeAttnParams p, const int* __restrict__ n_entries, const 
     }
 }
 
+// The same streams for many prompts, one workgroup per (prompt, head), in two
+// passes: a wave first scores all keys of its streams, its scores and each
+// round's max kept in LDS, then walks the streams over the values.  A wave reads
+// only what it wrote, so there is no barrier before the join.
+//
+// With either the keys or the values of one round in registers 8 workgroups a CU
+// are resident instead of 4, and it is they that hide the loads: the next
+// round's loads issued early take registers and cost (100 prompts 65.9 us, against
+// 58.7), and the one-pass kernel above, with its own q, k, v reduction, 69.5 where
+// this and the reduction's launch take 64.2 (keys and values 370 MB, 6.3 TB/s).  In
+// us, that kernel / this one with the reduction: 100 prompts of 2,000 rows 578 / 558;
+// 320 of 100 to 650 214 / 190; 512 of 90 162 / 118; 256 of 100 to 650, 16 heads of 64
+// dimensions, 54.8 / 47.
+template <int HD>
+__global__ void __launch_bounds__(256, 8)
+decode_attn_many_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ kp, const bf16_t* __restrict__ vp,
+                        const bf16_t* __restrict__ kn, const bf16_t* __restrict__ vn, const int* __restrict__ cu, int T,
+                        int P, int H, int max_keys, int max_new, int step, float scale_log2, bf16_t* __restrict__ o) {
+    constexpr int G = HD / 8, RPL = 64 / G, U = kLoads;
+    constexpr int KW = kWaveKeys<HD>;
+    constexpr int ST = HD + 2;
+    extern __shared__ float lds[];
+    const int seq = blockIdx.x / H, head = blockIdx.x - seq * H;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane % G, rg = lane / G;
+    const PromptKeys w = prompt_keys(cu, seq, T, P, step, max_keys);
+    const int nk = w.nk, PL = P + w.L, ld = H * HD;
+    const int rounds = (nk + KW - 1) / KW;      // of all streams; round b is of stream b mod n_streams
+    const int n_parts = key_parts(nk, kChunk<HD>), n_streams = 4 * n_parts;
+    const int most = (max_keys + KW - 1) / KW;
+    float* score = lds;                         // [most][KW]
+    float* top = lds + most * KW;               // [most] max of a round's scores
+    float* streams = top + ((most + 1) & ~1);   // [n_streams][ST]
+    const int lane_off = rg * ld + 8 * c;
+    auto load = [&](u32x4_t (&x)[U], const bf16_t* prompt_base, const bf16_t* new_base, int b) __attribute__((always_inline)) {
+        const int k0 = b * KW;
+        if (k0 + KW <= P || (k0 >= P && k0 + KW <= PL)) {   // rows in sequence (wave-uniform)
+            const bf16_t* r = prompt_base + (size_t)(k0 < P ? k0 : w.s0 + k0 - P) * ld + head * HD;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                x[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(r + RPL * u * ld + lane_off));
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {   // past the last key: its row, not used
+                const int j = min(k0 + rg + RPL * u, nk - 1);
+                const bool old = j < PL;
+                const int r = old ? (j < P ? j : w.s0 + j - P) : seq * max_new + (j - PL);
+                x[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(
+                    (old ? prompt_base : new_base) + ((size_t)(unsigned)r * (unsigned)ld + head * HD + 8 * c)));
+            }
+        }
+    };
+    {
+        float qf[8];
+        const u32x4_t qw = *reinterpret_cast<const u32x4_t*>(q + (size_t)seq * ld + head * HD + 8 * c);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            qf[2 * i] = bf16_lo(qw[i]);
+            qf[2 * i + 1] = bf16_hi(qw[i]);
+        }
+        for (int b = wave; b < rounds; b += 4) {
+            u32x4_t kw[U];
+            load(kw, kp, kn, b);
+            const int j0 = b * KW + rg;
+            float mr = -INFINITY;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                float a = 0.f;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    a = fmaf(bf16_lo(kw[u][i]), qf[2 * i], a);
+                    a = fmaf(bf16_hi(kw[u][i]), qf[2 * i + 1], a);
+                }
+                a = group_sum<G>(a) * scale_log2;
+                a = j0 + RPL * u < nk ? a : -INFINITY;
+                if (c == 0) score[j0 + RPL * u] = a;
+                mr = fmaxf(mr, a);
+            }
+#pragma unroll
+            for (int s = G; s < 64; s <<= 1) mr = fmaxf(mr, __shfl_xor(mr, s));
+            if (lane == 0) top[b] = mr;
+        }
+    }
+    __builtin_amdgcn_wave_barrier();   // LDS is in order within a wave
+    for (int s = wave; s < n_streams; s += 4) {
+        float m = -INFINITY, l = 0.f, acc[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+        for (int b = s; b < rounds; b += n_streams) {
+            u32x4_t vw[U];
+            load(vw, vp, vn, b);
+            const float mr = fmaxf(m, top[b]);
+            const float f = exp2_ref(m, mr);
+            m = mr;
+            l *= f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[i] *= f;
+            float pr[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) pr[u] = exp2_ref(score[b * KW + rg + RPL * u], m);
+            auto add = [&](int u) __attribute__((always_inline)) {
+                l += pr[u];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    acc[2 * i] = fmaf(pr[u], bf16_lo(vw[u][i]), acc[2 * i]);
+                    acc[2 * i + 1] = fmaf(pr[u], bf16_hi(vw[u][i]), acc[2 * i + 1]);
+                }
+            };
+            if (b * KW + KW <= nk) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) add(u);
+            } else {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (b * KW + rg + RPL * u < nk) add(u);
+            }
+        }
+        end_stream<HD>(acc, l, m, lane, streams + s * ST);
+    }
+    __syncthreads();
+    if (tid < HD) o[(size_t)seq * ld + (size_t)head * HD + tid] = join_streams<HD>(streams, n_parts, tid);
+}
+
 }  // namespace
 
 int decode_chunk(int hd) { return hd == 128 ? kChunk<128> : kChunk<64>; }
@@ -432,6 +608,25 @@ constexpr int64_t kWholeItems = 1024;
 static bool whole_prompts(int64_t n_seq, int n_heads) { return n_seq * n_heads >= kWholeItems; }
 static int64_t entries_of(int64_t n_seq, int64_t max_keys, int n_heads, int hd) {
     return whole_prompts(n_seq, n_heads) ? n_seq : n_seq * key_parts((int)max_keys, decode_chunk(hd));
+}
+
+// LDS of the two-pass kernel: scores, a max per round, the streams.
+static size_t many_lds(int max_keys, int hd) {
+    const int kw = hd == 128 ? kWaveKeys<128> : kWaveKeys<64>;
+    const int most = (max_keys + kw - 1) / kw;
+    return ((size_t)most * kw + ((most + 1) & ~1) + 4 * (size_t)key_parts(max_keys, decode_chunk(hd)) * (hd + 2)) * sizeof(float);
+}
+constexpr size_t kCuLds = 160 * 1024;
+
+// More than the eight workgroups a CU that the two-pass kernel's registers let in (a
+// layer's step in us, one pass / two passes with the reduction's launch: 32 heads of 128
+// dimensions, 64 prompts of 100 to 650 rows 165 / 168, 80 183 / 181, 100 200 / 199, 160 280
+// / 271; 16 heads 128 112.5 / 113.6, 160 140.5 / 135.3; 16 heads of 64 dimensions 112 69.2 /
+// 70.2, 128 73.4 / 72.6), and at least six of them in LDS (100 prompts of 2,000 rows 714 /
+// 694; of 4,000, four a CU, 1,229 / 1,233).
+bool decode_many(int n_seq, int n_heads, int hd, int max_keys) {
+    const int64_t items = (int64_t)n_seq * n_heads;
+    return items > 2048 && items < (1ll << 31) && many_lds(max_keys, hd) <= kCuLds / 6;
 }
 
 // What a workspace holds is for n_seq prompts or any fewer, so that it never
@@ -492,6 +687,15 @@ hipError_t launch_decode_attention(const uint16_t* q, const DecodeQkv& qkv, cons
     p.list = list;
     p.o = o;
     p.whole = whole_prompts(n_seq, n_heads) ? 1 : 0;
+    if (!qkv.part && decode_many(n_seq, n_heads, hd, max_keys)) {
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(n_seq * n_heads)), dim3(256), many_lds(max_keys, hd), st, q, kp, vp,
+                               kn, vn, cu, T, n_prefix, n_heads, max_keys, max_new, step, p.scale_log2, o);
+        };
+        if (hd == 128) launch(decode_attn_many_kernel<128>);
+        else launch(decode_attn_many_kernel<64>);
+        return hipGetLastError();
+    }
     int64_t wgs = entries_of(n_seq, max_keys, n_heads, hd) * n_heads;   // those past the list's end leave
     if (wgs > (1 << 20)) wgs = 1 << 20;
     const dim3 grid((unsigned)wgs);

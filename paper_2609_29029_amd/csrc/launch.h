@@ -140,6 +140,9 @@ struct DecodeQkv {
     const int* pos;
     int n_pos;
 };
+// Whether launch_decode_attention runs its kernel for many prompts, which wants q
+// rotated and k and v in their slot (no qkv.part).
+bool decode_many(int n_seq, int n_heads, int hd, int max_keys);
 // one query per prompt over its prefill keys kp/vp [T][H*hd] and slots 0..step of
 // kn/vn; with qkv.part it first rotates the new token's q and k and writes its k
 // and v into slot `step`
@@ -162,6 +165,11 @@ hipError_t launch_skinny_gemm(const uint16_t* a, const uint16_t* b0, const uint1
 // x += sum of partials [slots][M][d]; with h, h = bf16(RMSNorm(x) * g)
 hipError_t launch_skinny_resid_norm(const float* part, SkinnySplit sp, int M, int d, float* x, const uint16_t* g,
                                     uint16_t* h, float eps, hipStream_t st);
+// q to q[M][d], k and v to slot `step` of kc, vc [M][max_new][d], RoPE at pos[m]
+// over heads of hd (128 or 64) dimensions
+hipError_t launch_skinny_qkv(const float* part, SkinnySplit sp, int M, int d, int hd, const float2* rope, const int* pos,
+                             int n_pos, uint16_t* q, uint16_t* kc, uint16_t* vc, int max_new, int step,
+                             hipStream_t st);
 // a[M][F] = silu(gate) * up
 hipError_t launch_skinny_swiglu(const float* part, SkinnySplit sp, int M, int F, uint16_t* a, hipStream_t st);
 

@@ -47,6 +47,12 @@ __device__ __forceinline__ float2 rope_entry(int p, int j, int hd, double base) 
     return make_float2((float)cos(ang), (float)sin(ang));
 }
 
+// Rotate-half RoPE of one pair, the fused forms written out: kernels that rotate
+// the same row must round alike.
+__device__ __forceinline__ float2 rotate_pair(float x1, float x2, float2 cs) {
+    return make_float2(fmaf(x1, cs.x, -(x2 * cs.y)), fmaf(x2, cs.x, x1 * cs.y));
+}
+
 constexpr int kWave = 64;
 
 }  // namespace rift

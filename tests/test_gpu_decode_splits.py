@@ -43,6 +43,10 @@ CASES = [   # heads, head_dim, ffn, prompt rows, prefix rows, step
     (8, 128, 1024, [2 + 5 * i for i in range(129)], 35, 3),     # 129 rows, prompts whole
     (8, 128, 1024, [1 + i % 40 for i in range(257)], 0, 0),     # two row tiles
     (16, 64, 1024, [1 + 17 * i for i in range(64)], 0, 0),      # whole, 64-dimensional heads
+    # more than 2,048 workgroups: the two-pass kernel; round, part and stream edges
+    (8, 128, 1024, [0, 1, 15, 16, 17, 63, 64, 127, 128, 129, 512, 700, 1030] + [3 + 2 * i for i in range(250)], 0, 2),
+    (8, 128, 1024, [1 + i % 70 for i in range(260)], 35, 1),    # prefix rows inside a round
+    (16, 64, 1024, [0, 31, 32, 33, 255, 256, 257, 1100] + [2 + 3 * i for i in range(130)], 16, 0),
 ]
 
 
