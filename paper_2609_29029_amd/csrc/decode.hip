@@ -601,10 +601,13 @@ decode_attn_many_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__
 
 int decode_chunk(int hd) { return hd == 128 ? kChunk<128> : kChunk<64>; }
 
-// A workgroup takes a prompt whole where that gives each CU four (100 prompts, 32
-// heads: 67 us against 74 in parts of 128 keys; one prompt in parts 9, the 32 workgroups of one
-// taken whole read its keys on an eighth of the chip).
-constexpr int64_t kWholeItems = 1024;
+// A workgroup takes a prompt whole from two workgroups a CU on: parts cost a join
+// across workgroups.  In parts / whole, two layers' step in us: 31 prompts of 2,000
+// rows and 32 heads 670 / 566, 16 of them 436 / 389, 16 of 100 to 650 236 / 228, 32 with 16
+// heads of 64 dimensions 97.9 / 94.8; with half as many workgroups 8 prompts of 100 to 650
+// 221 / 215, 16 with 16 heads of 64 84.2 / 85.9; one prompt of 647 rows 199 in parts, the 32
+// workgroups of one taken whole read its keys on an eighth of the chip.
+constexpr int64_t kWholeItems = 512;
 static bool whole_prompts(int64_t n_seq, int n_heads) { return n_seq * n_heads >= kWholeItems; }
 static int64_t entries_of(int64_t n_seq, int64_t max_keys, int n_heads, int hd) {
     return whole_prompts(n_seq, n_heads) ? n_seq : n_seq * key_parts((int)max_keys, decode_chunk(hd));

@@ -39,7 +39,8 @@ CASES = [   # heads, head_dim, ffn, prompt rows, prefix rows, step
     (8, 128, 2816, [0, 1, 63, 64, 127, 128, 129, 255, 256, 511, 512, 700, 1030], 0, 0),
     (8, 128, 2176, [5, 300, 900] * 11, 7, 2),            # 33 rows; runs that cross tiles unevenly
     (16, 64, 3456, [0, 127, 254, 255, 256, 700, 1100, 2100], 3, 1),
-    (8, 128, 1024, [3 + 11 * i for i in range(66)], 0, 1),      # 66 rows, parts
+    (8, 128, 1024, [3 + 11 * i for i in range(66)], 0, 1),      # 66 rows, prompts whole
+    (8, 128, 1024, [7 + 19 * i for i in range(63)], 0, 1),      # the most that are taken in parts
     (8, 128, 1024, [2 + 5 * i for i in range(129)], 35, 3),     # 129 rows, prompts whole
     (8, 128, 1024, [1 + i % 40 for i in range(257)], 0, 0),     # two row tiles
     (16, 64, 1024, [1 + 17 * i for i in range(64)], 0, 0),      # whole, 64-dimensional heads
