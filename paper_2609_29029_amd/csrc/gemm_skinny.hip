@@ -11,8 +11,9 @@
 //                   (slot: which of the tile's workgroups it is).  Only the 32-row
 //                   blocks of A that hold prompts are staged, so the LDS goes to
 //                   stages of B: 6 in flight (96 KB a CU) up to 32 prompts, 3 (48
-//                   KB) up to 128.  Products by v_mfma_f32_32x32x16_bf16, each wave
-//                   32 columns.
+//                   KB) up to 128.  More prompts are blocks of 128 to 256 rows,
+//                   each a pass over the weights.  Products by
+//                   v_mfma_f32_32x32x16_bf16, each wave 32 columns.
 //   reduce kernels  add the partials of every output in slot order and do
 //                   the layer's elementwise work: residual add then RMSNorm of
 //                   the updated row; SiLU(gate) * up.  (Rotation of q and k is done
@@ -424,7 +425,18 @@ hipError_t launch_skinny_gemm(const uint16_t* a, const uint16_t* b0, const uint1
     if (M <= 32) return launch(skinny_gemm_kernel<1, 1, 7>, 32, 256);
     if (M <= 64) return launch(skinny_gemm_kernel<1, 2, 6>, 64, 512);
     if (M <= 128) return launch(skinny_gemm_kernel<2, 2, 4>, 128, 512);
-    return launch(skinny_gemm_kernel<4, 2, 3>, 256, 512);
+    // More than 128 prompts: blocks of 128 rows, two workgroups a CU, so that two blocks
+    // read the same weights beside each other; where there is a run for every CU also
+    // one workgroup a CU with blocks of 192 or 256 rows, if these pad no more.  A layer's
+    // step in us, blocks of 128 / 192 / 256 rows (256 is what ran before): d = 4,096, 129
+    // prompts 202 / 188 / 205, 193 232 / 303 / 229, 320 373 / 352 / 387, 512 469 / 513 /
+    // 465, 640 609 / 656 / 628, 1,000 907 / 987 / 883; d = 2,048, 129 102 / 95 / 103, 320
+    // 166 / 167 / 180, 512 225 / 241 / 226; d = 1,024 129 62 / 64 / 69, 256 75 / 81 / 82.
+    const auto padded = [&](int rows) { return (M + rows - 1) / rows * rows; };
+    const bool full = p.sp.wgs == kSkinnyWgs;
+    if (full && M <= 384 && padded(192) <= padded(128)) return launch(skinny_gemm_kernel<3, 2, 3>, 192, 512);
+    if (full && M > 384 && padded(256) == padded(128)) return launch(skinny_gemm_kernel<4, 2, 3>, 256, 512);
+    return launch(skinny_gemm_kernel<2, 2, 2>, 128, 512);
 }
 
 bool skinny_norm_supported(int d) {

@@ -42,7 +42,10 @@ CASES = [   # heads, head_dim, ffn, prompt rows, prefix rows, step
     (8, 128, 1024, [3 + 11 * i for i in range(66)], 0, 1),      # 66 rows, prompts whole
     (8, 128, 1024, [7 + 19 * i for i in range(63)], 0, 1),      # the most that are taken in parts
     (8, 128, 1024, [2 + 5 * i for i in range(129)], 35, 3),     # 129 rows, prompts whole
-    (8, 128, 1024, [1 + i % 40 for i in range(257)], 0, 0),     # two row tiles
+    (8, 128, 1024, [1 + i % 40 for i in range(257)], 0, 0),     # three blocks of 128 rows
+    (16, 128, 5504, [1 + i % 30 for i in range(190)], 0, 0),    # one block of 192 rows, and two of them
+    (16, 128, 5504, [1 + i % 30 for i in range(260)], 0, 0),
+    (16, 128, 5504, [1 + i % 30 for i in range(500)], 0, 0),    # two of 256
     (16, 64, 1024, [1 + 17 * i for i in range(64)], 0, 0),      # whole, 64-dimensional heads
     # more than 2,048 workgroups: the two-pass kernel; round, part and stream edges
     (8, 128, 1024, [0, 1, 15, 16, 17, 63, 64, 127, 128, 129, 512, 700, 1030] + [3 + 2 * i for i in range(250)], 0, 2),
