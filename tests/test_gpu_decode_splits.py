@@ -101,3 +101,59 @@ def test_decode_splits(H, hd, ffn, lens, P, step):
         alone, slot1 = decode(cu1, 1, kv1, new[:, :, i:i + 1].contiguous(), x[i:i + 1], kv1.shape[2])
         assert torch.equal(alone[0], out[i]), (i, lens[i])
         assert torch.equal(slot1[0, :, 0], slots[0, :, i])
+
+
+LAYERS = [   # heads, head_dim, ffn, prompt rows, layers: prompts in parts, whole, and many
+    (8, 128, 2816, [129, 300, 700, 1100], 3),
+    (16, 64, 2816, [129, 257, 700, 1100], 3),
+    (16, 128, 4096, [1100, 129, 640], 2),
+    (10, 128, 2560, [129, 300, 700, 1100], 3),                  # widths without split K: q, k, v in memory
+    (20, 64, 2560, [257, 300, 700, 1100], 3),
+    (20, 64, 2560, [257, 300, 700, 1100] * 7, 2),               # whole
+    (10, 128, 2560, [129, 300, 700, 1100] * 13, 2),
+    (20, 64, 2560, [257, 40, 300, 700, 3] * 21, 2),             # two passes
+    (10, 128, 2560, [129, 40, 300, 700, 3] * 42, 2),
+    (8, 128, 2816, [129, 40, 300, 700, 3] * 52, 3),
+]
+
+
+@pytest.mark.parametrize("H,hd,ffn,lens,n_layers", LAYERS)
+def test_decode_through_layers(H, hd, ffn, lens, n_layers):
+    """Several layers with weights and caches of their own: what a layer's attention
+    leaves behind (its arrival counters) must not reach the next."""
+    import paper_2609_29029_amd as R
+    torch = torch_mod()
+    d, n = H * hd, len(lens)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(H + n)
+    mk = lambda *s, std=1.0, mean=0.0: torch.empty(*s, device="cuda", dtype=torch.bfloat16).normal_(mean, std, generator=g)
+    shape = dict(wq=(d, d), wk=(d, d), wv=(d, d), wo=(d, d), w_gate=(ffn, d), w_up=(ffn, d), w_down=(d, ffn))
+    Ws = [{k: mk(*s, std=0.03) for k, s in shape.items()} for _ in range(n_layers)]
+    for W in Ws:
+        W["g_attn"], W["g_ffn"] = mk(d, std=0.05, mean=1.0), mk(d, std=0.05, mean=1.0)
+    cfg = R.model_cfg(d, H, hd, ffn, n_layers, 1e-6, 10000.0, R.RIFT_BF16)
+    cu = np.concatenate([[0], np.cumsum(lens)])
+    kv, x = mk(n_layers, 2, int(cu[-1]), d), mk(n, d)
+
+    def decode(cu, x, kv):
+        m = len(cu) - 1
+        slots = torch.full((n_layers, 2, m, 1, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        ws = torch.empty(R.rift_decode_workspace_size(cfg, m, max(lens), 1), dtype=torch.uint8, device="cuda")
+        ws.fill_(255)
+        out = torch.empty(m, d, device="cuda")
+        R.rift_decode_step(cfg, Ws, x, torch.tensor(cu, dtype=torch.int32, device="cuda"), kv.shape[2], max(lens), kv,
+                           slots, 0, out, ws)
+        return out, slots
+
+    out, slots = decode(cu, x, kv)
+    for i in sorted({0, 1, 2, 3, n // 2, n - 1} & set(range(n))):
+        rows = kv[:, :, cu[i]:cu[i + 1]]
+        ref = x[i].double()
+        for l in range(n_layers):
+            ref, k, v = _reference(torch, Ws[l], ref, rows[l, 0], rows[l, 1], H, hd, float(lens[i]))
+            # as above for one layer; the roundings of the layers before add to it
+            for got, want in ((slots[l, 0, i, 0], k), (slots[l, 1, i, 0], v)):
+                assert float((got.double() - want).norm() / want.norm()) <= 1e-2 * (l + 1), (i, l)
+        assert float((out[i].double() - ref).norm() / ref.norm()) <= 1e-2 * n_layers, i
+        alone, slot = decode([0, lens[i]], x[i:i + 1], rows.contiguous())
+        assert torch.equal(alone[0], out[i]) and torch.equal(slot[:, :, 0], slots[:, :, i]), i

@@ -121,3 +121,18 @@ def test_f32_attends_in_sequences_longer_than_declared(hd):
     whole, _ = prefill_f32(lens, x, W, cfg, positions=positions)
     short, _ = prefill_f32(lens, x, W, cfg, positions=positions, max_seqlen=17)
     assert np.array_equal(whole, short)
+
+
+@pytest.mark.parametrize("d,hd,ffn,lens", [
+    # more than 4,096 tiles in each product: 64-row tiles, the last one partial (2,117 and
+    # 1,497 rows); 65 column tiles of gate/up, so the last pair is a single one
+    (1024, 64, 1040, [40] + [300] * 6 + [277]),
+    (1536, 128, 1552, [300] * 4 + [297]),
+])
+def test_f32_rows_of_the_tile_kernel_are_those_of_the_split_kernel(d, hd, ffn, lens):
+    W, cfg = small_model(d, hd, ffn)
+    x = np.random.default_rng(d).standard_normal((sum(lens), d)).astype(np.float32)
+    hid, cu = prefill_f32(lens, x, W, cfg)
+    for i in range(len(lens)):
+        alone, _ = prefill_f32(lens[i:i + 1], x[cu[i]:cu[i + 1]], W, cfg)
+        assert np.isfinite(alone).all() and np.array_equal(hid[cu[i]:cu[i + 1]], alone), i
