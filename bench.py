@@ -28,12 +28,12 @@ METRIC = "retained vision tokens prefilled/sec + ms per 400-tile scene query, 1 
 PEAK_BF16_TFLOPS = 2516.6      # MI355X dense bf16 MFMA: 256 CU x 2.4 GHz x 4096 flop/clk
 PEAK_HBM_GBS = 8000.0          # MI355X HBM3E
 STAGES = ("qkv_rope", "attention", "out_proj", "gate_up_swiglu", "down_proj")
-# (each GEMM adds a half-tile tail launch when its last round over the CUs is at most half full)
-KERNEL_NAMES = {"qkv_rope": "QKV+RoPE GEMM (gemm_bf16_pp_kernel<0>)",
+# (at this workload; the tile heights and a short-tile tail follow the row count)
+KERNEL_NAMES = {"qkv_rope": "QKV+RoPE GEMM (gemm_bf16_pp_kernel<0, 8>)",
                 "attention": "varlen causal attention (attn_bf16_kernel)",
-                "out_proj": "output projection + residual (gemm_bf16_pp_kernel<1>)",
-                "gate_up_swiglu": "gate/up+SwiGLU GEMM (gemm_bf16_pp_kernel<2>)",
-                "down_proj": "down projection + residual (gemm_bf16_pp_kernel<1>)"}
+                "out_proj": "output projection + residual (gemm_bf16_pp_kernel<1, 8>)",
+                "gate_up_swiglu": "gate/up+SwiGLU GEMM (gemm_bf16_pp_kernel<2, 8>)",
+                "down_proj": "down projection + residual (gemm_bf16_pp_kernel<1, 8>)"}
 GEMM_SRC = os.path.join(ROOT, "paper_2609_29029_amd", "csrc", "gemm_bf16.hip")
 
 # HBM traffic of one gate/up+SwiGLU launch at the 400-tile workload with the shared
@@ -479,8 +479,10 @@ def merge_run(R, torch, w, tokens, qbank, sysd, qryd, layers, q, reps=3) -> dict
     """The scene-query with each budget split into dominant and contextual
     tokens (VisionZip's merge of the remainder, 54 + 10 at 64): the same
     prompt lengths, plus the merge.  Median device time of the merge call and
-    of the whole query over `reps` queries; the merge's float64 work is the
-    canonical dot of every non-target remaining token with every target."""
+    of the whole query over `reps` queries, and the merge's HBM rate over the
+    bytes it cannot do without: every remaining token read once to be assigned
+    and once for its group's mean (all of them are known only after the last is
+    assigned, and they do not fit a cache), the contextual rows written."""
     from paper_2609_29029_amd.pipeline import SceneQuery
     mq = SceneQuery(tokens, qbank, sysd, qryd, layers, q.shape, w.keep_count, w.tau, w.levels,
                     w.tier_num, w.tier_den, with_sims=True, merge=(10, 64), shared_prefix=q.shared)
@@ -503,13 +505,15 @@ def merge_run(R, torch, w, tokens, qbank, sysd, qryd, layers, q, reps=3) -> dict
         tq.append(ev[0].elapsed_time(ev[3]))
     assert mq.check_status() == [0, 0, 0]
     dom, ctx = R.rift_split_budgets(mq.budgets_host, w.n_v)
-    fma = sum(int(w.n_v - kd - kc) * int(kc) * w.model.d for kd, kc in zip(dom, ctx) if kc > 1)
+    rest = sum(w.n_v - int(kd) for kd, kc in zip(dom, ctx) if kc > 0)
     ms = statistics.median(tm)
+    row = w.model.d * 2
+    nbytes = (2 * rest + int(mq.n_context)) * row
     return {"ms_per_query": round(statistics.median(tq), 2), "merge_ms": round(ms, 4),
             "dominant_tokens": int(mq.n_dominant), "contextual_tokens": int(mq.n_context),
             "retained_vision_tokens": int(mq.n_selected),
-            "fp64_fma": fma, "fp64_TFLOPs": round(2 * fma / (ms * 1e-3) / 1e12, 2),
-            "frac_fp64_vector_peak": round(2 * fma / (ms * 1e-3) / 1e12 / 78.6, 4)}
+            "bytes": nbytes, "GBs": round(nbytes / (ms * 1e-3) / 1e9, 1),
+            "frac_hbm": round(nbytes / (ms * 1e-3) / 1e9 / PEAK_HBM_GBS, 4)}
 
 
 def decode_run(R, torch, w, q, steps=8) -> dict:

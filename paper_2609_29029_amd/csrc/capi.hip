@@ -706,8 +706,9 @@ rift_status rift_prefill(const rift_model_cfg* cfg, const rift_layer_weights* la
 
 namespace {
 // decode workspace: RoPE table over max_seqlen + max_new positions, the new
-// tokens' positions, h, q, k, v [n_seq][d], the SwiGLU activation [n_seq][ffn], the
-// GEMMs' partial sums, and the attention's work list, counters and chunk results
+// tokens' positions, h, q (without split K also k and v) [n_seq][d], the SwiGLU
+// activation [n_seq][ffn], the GEMMs' partial sums, and the attention's work list,
+// counters and chunk results
 struct DecodeLayout {
     size_t rope, pos, h, q, k, v, a, part, n_list, list, arrived, lpart, total;
 };
@@ -737,10 +738,12 @@ DecodeLayout decode_layout(const rift_model_cfg& c, int64_t n_seq, int64_t n_pos
     off += align_up((size_t)n_seq * c.d * 2);
     L.q = off;
     off += align_up((size_t)n_seq * c.d * 2);
-    L.k = off;
-    off += align_up((size_t)n_seq * c.d * 2);
-    L.v = off;
-    off += align_up((size_t)n_seq * c.d * 2);
+    if (!decode_skinny(c)) {   // else they go to the cache slot straight away
+        L.k = off;
+        off += align_up((size_t)n_seq * c.d * 2);
+        L.v = off;
+        off += align_up((size_t)n_seq * c.d * 2);
+    }
     L.a = off;
     off += align_up((size_t)n_seq * c.ffn * 2);
     L.part = off;
@@ -830,7 +833,6 @@ rift_status rift_decode_step(const rift_model_cfg* cfg, const rift_layer_weights
         qkv.part = many ? nullptr : part;
         qkv.sp = s_qkv;
         qkv.rope = rope;
-        qkv.pos = pos;
         qkv.n_pos = n_pos;
         RIFT_TRY(launch_rmsnorm(x_new, true, hidden_out, layers[0].g_attn, true, h, true, n_seq, d, c.rms_eps, st));
         for (int l = 0; l < c.n_layers; ++l) {

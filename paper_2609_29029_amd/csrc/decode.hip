@@ -4,8 +4,9 @@
 // to the generated tokens' own, kept in a decode cache slot per step.  With a
 // shared prefix of P rows (the prefill's sequence 0), a prompt's keys are the
 // P prefix rows followed by its own rows, and L_i counts both.  The
-// decoder layers are those of the prefill (Sec. 2.1; LLaMA-7B shape); the
-// per-token GEMMs run on the prefill's kernels with M = n_seq.
+// decoder layers are those of the prefill (Sec. 2.1; LLaMA-7B shape); their
+// GEMMs are split-K products where the width is 1,024 times a power of two, and
+// the prefill's kernels with M = n_seq elsewhere.
 //
 //   decode_prep    position of each prompt's new token, L_i + step; the RoPE
 //                  table; the attention's work list and cleared counters
@@ -154,8 +155,7 @@ struct DecodeAttnParams {
     DecodeQkv qkv;
     const bf16_t *kp, *vp;
     bf16_t *kn, *vn;
-    const int* cu;
-    int n_seq, T, P, H, max_keys, max_new, step;
+    int n_seq, P, H, max_new, step;
     float scale_log2;
     int whole;             // a workgroup takes all parts of a prompt
     DecodeList list;
@@ -678,12 +678,9 @@ hipError_t launch_decode_attention(const uint16_t* q, const DecodeQkv& qkv, cons
     p.vp = vp;
     p.kn = kn;
     p.vn = vn;
-    p.cu = cu;
     p.n_seq = n_seq;
-    p.T = T;
     p.P = n_prefix;
     p.H = n_heads;
-    p.max_keys = max_keys;
     p.max_new = max_new;
     p.step = step;
     p.scale_log2 = 1.4426950408889634f / sqrtf((float)hd);

@@ -58,10 +58,11 @@ struct GemmParams {
     const float2* rope;
     const int* pos;
     int n_pos;
-    int num_m, num_n;   // 256x256 output tiles
-    int n_full;         // tiles 0 .. n_full-1 (grouped order) run as whole tiles,
-                        // the rest as two 256x128 halves each
-    int reverse;        // walk the whole tiles from the last to the first
+    int num_m, num_n;   // output tiles of the launch's plan: 32 MB rows by 256 columns
+                        // (short tiles: by 128)
+    int n_full;         // tiles 0 .. n_full-1 (grouped order) run on the ping-pong
+                        // kernel, the rest as the short tiles of a tail
+    int reverse;        // walk the tiles from the last to the first
 };
 
 // Workgroup bid of a launch of `count` workgroups -> its index in that launch,
@@ -134,8 +135,8 @@ __device__ __forceinline__ int b_row(const GemmParams& p, int n0, int r) {
     }
 }
 
-// Same, saddr form: 64-bit wave-uniform base plus a 32-bit per-lane byte
-// offset (the hardware adds them; offsets stay below 2^31 by the host checks).
+// LDS DMA (global_load_lds_dwordx4): 16 bytes per lane to LDS address lds_addr +
+// 16 lane, from a 64-bit wave-uniform base plus a 32-bit per-lane byte offset (the hardware adds them; offsets stay below 2^31 by the host checks).
 __device__ __forceinline__ void dma16s(const void* base, uint32_t voff, uint32_t lds_addr) {
     const uint64_t b = (uint64_t)(uintptr_t)base;
     // readfirstlane returns a signed int: go through uint32_t so the low word is
@@ -741,9 +742,12 @@ struct GemmPlan {
 
 // Time of one 64-deep stage of a tile with the chip busy and weights cold (ns),
 // what a tile costs besides its stages (first DMA, epilogue) and what the
-// second launch of a tail costs besides its tiles.  From sweeps of every plan
-// over M = 176 .. 18,739 and widths 512 .. 4,096; the pick was within 5% of the
-// fastest plan in all of them.  At d = 4,096, FFN 11,008 (us; the first figure
+// second launch of a tail costs besides its tiles.  Against every plan in turn, the
+// four products of d = 1,024, 2,048, 2,560 and 4,096 at M = 40 to 18,739 (208 products):
+// the pick was within 5% of the fastest in 205, and 7% (d = 2,560, M = 1,000, q, k, v)
+// and 13% off (the same with M = 643: 51 us as short tiles against 45 as 160-row
+// ones; d = 4,096, M = 2,000: 181 with a tail against 161 as 224-row tiles) in the
+// others.  At d = 4,096, FFN 11,008 (us; the first figure
 // the 256-row tiles alone): M = 643 QKV 93 -> 89 (160-row tiles), out 82 -> 33
 // and down 221 -> 76 (128-row short tiles), gate/up 155 -> 113 (two of 258 tiles
 // as a tail); M = 3,075 (16 prompts) 283 -> 257, 94 -> 90, 450 -> 414 and

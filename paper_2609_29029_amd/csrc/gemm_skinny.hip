@@ -39,7 +39,9 @@ namespace {
 constexpr int SK_BN = 128;   // columns per tile (4 waves x 32)
 constexpr int SK_KS = 64;    // k per stage
 constexpr int SK_RB = 128;   // bytes of one operand row of a stage
-constexpr int kSkinnyWgs = 256;       // workgroups of a launch, one per CU, at most
+// Workgroups of a launch, one for each CU of the whole GPU, at most.  Not asked of the
+// device: the runs fix a row's rounding and the workspace's size.
+constexpr int kSkinnyWgs = 256;
 constexpr int kSkinnyMaxSplit = 16;   // workgroups per tile where the tiles are few
 constexpr int kSkinnyMinStages = 4;   // runs of at least 256 k
 

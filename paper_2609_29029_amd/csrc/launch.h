@@ -137,7 +137,6 @@ struct DecodeQkv {
     const float* part;     // [slots][n_seq][3 d]; null: q, kn and vn hold them
     SkinnySplit sp;
     const float2* rope;
-    const int* pos;
     int n_pos;
 };
 // Whether launch_decode_attention runs its kernel for many prompts, which wants q

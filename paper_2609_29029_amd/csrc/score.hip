@@ -476,13 +476,16 @@ size_t rank_lds_bytes(int n_tiles) {
 }
 
 // Whether a wave takes 16 tokens instead of 32, from the workgroups that 32-token
-// sets make.  A workgroup alone on its CU takes 55 us with 32-token sets and 38
-// with 16 (d = 4,096), two on a CU 100 and 61, three of the 16-token ones 88; so 16
-// tokens pay where they still leave one workgroup a CU (8 tiles: 54 -> 38 us) and
-// where 32 would put two on some CUs and 16 at most three on any (64 tiles: 92.5 ->
-// 88; d = 1,024 36.5 -> 32).  Elsewhere 32 tokens win (100 tiles 103 against 117 us,
-// 400 tiles 370 against 403): the background direction w is widened to float64
-// once for twice the tokens.
+// sets make (on the 256 CUs of the whole GPU).  A workgroup alone on its CU takes 55 us
+// with 32-token sets and 38 with 16 (bfloat16, d = 4,096), two on a CU 100 and 61, three of
+// the 16-token ones 88; so 16 tokens pay where they still leave one workgroup a CU and where
+// 32 would put two on some CUs and 16 at most three on any.  Elsewhere 32 tokens win: the
+// background direction w is widened to float64 once for twice the tokens.  In us, 32 / 16,
+// 576 tokens a tile: bfloat16 8 tiles 53.9 / 38.2, 36 54.8 / 60.8, 64 91.8 / 86.9, 85 97.9 /
+// 96.0, 100 104 / 116, 400 367 / 393 (d = 1,024: 8 23.9 / 19.4, 64 35.8 / 32.4, 100 39.1 /
+// 40.9); float32, the same line within 3% but for 30 to 56 tiles, 8 110 / 88, 36 154 / 140, 64
+// 199 / 195, 85 208 / 213, 100 230 / 278, 200 450 / 568 (d = 1,024: 8 40.0 / 32.9, 64 60.9 /
+// 59.1, 100 76.2 / 79.6).
 inline bool small_sets(long long wgs32) {
     constexpr long long kCus = 256;
     return 2 * wgs32 <= kCus || (wgs32 > kCus && 2 * wgs32 <= 3 * kCus);
