@@ -15,7 +15,7 @@
 //                 products are fused-multiply-added in ascending k onto the
 //                 accumulator (checked bit for bit against that chain), i.e. the
 //                 canonical order.  400 tiles, d = 4,096: 150 us with one pair
-//                 per thread on the vector units before, 35 us now (49 without the
+//                 per thread on the vector units before, 30 us now (49 without the
 //                 next slice's loads in flight).
 //   knn_smooth    one wave per tile: cosines G_ij / sqrt(G_ii G_jj) (0 when
 //                 that is 0) in LDS, m rounds of a wave arg-max (largest
