@@ -10,12 +10,12 @@
 // and values from that XCD's L2 after the first fetch (HBM-side fetch per
 // layer 0.46 GB, the q, k and v bytes, against 0.79 GB when one workgroup
 // loops over a sequence's blocks and its later passes miss the L2).
-// Other head counts, few sequences (up to 128): the same workgroups and order,
-// without a list; each finds its entry from the sequences' lengths, and those of
-// the last group's missing heads leave.  (Nine prompts of 43 to 577 rows, 20 heads
-// of 64 dimensions: 21.8 us as one workgroup per (sequence, head), 12.2 so.)
-// Many sequences: one workgroup per (sequence, head), looping over the sequence's
-// 128-query blocks, the last (longest-running) first.  Wave w owns queries
+// Other head counts, few sequences: the same workgroups without a list; each finds
+// its entry from the sequences' lengths, the (sequence, head) pairs being dealt to
+// the XCDs in turn.  (Nine prompts of 43 to 577 rows, 20 heads of 64 dimensions: 21.8
+// us as one workgroup per (sequence, head), 12.2 so.)
+// Many or short sequences: one workgroup per (sequence, head), looping over the
+// sequence's 128-query blocks, the last (longest-running) first.  Wave w owns queries
 // [32 w, 32 w + 32) of a block (sequences in packing order, so prompts packed
 // longest first start first).  Keys and values stream 64 at a time through a ring of
 // S = 2 LDS stages that LDS DMA fills a block ahead, one barrier per block,
@@ -114,34 +114,37 @@ attn_bf16_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
 
     int seq, head, qb_top = -1;
     if constexpr (FROM == kScan) {
-        // entry e of the list below, found by each wave: the sequence whose blocks
-        // (times groups) hold it, 64 sequences at a time
-        const int hs = (H + 7) >> 3, lane_ = threadIdx.x & 63;
+        // Entry e of XCD x = blockIdx mod 8, found by each wave: the (sequence, head)
+        // pairs are dealt to the XCDs in turn, each with all of its blocks; sequence s
+        // has heads h0, h0 + 8, .. on x, h0 = (x - s H) mod 8.  64 sequences at a time.
+        const int lane_ = threadIdx.x & 63, x = (int)(blockIdx.x & 7);
         int e = (int)(blockIdx.x >> 3);
         seq = -1;
         for (int base = 0; base < n_seq; base += 64) {
             const int sq = base + lane_;
             const int len = sq < n_seq ? cu[sq + 1] - cu[sq] : 0;
             const int nb = len > 0 ? (len + BQ - 1) / BQ : 0;
-            int incl = nb * hs;
+            const int h0 = (int)((unsigned)(x - sq * H) & 7u);
+            int incl = nb * ((H - h0 + 7) >> 3);
+            const int own = incl;
 #pragma unroll
             for (int sh = 1; sh < 64; sh <<= 1) {
-                const int x = __shfl_up(incl, sh);
-                incl += lane_ >= sh ? x : 0;
+                const int t = __shfl_up(incl, sh);
+                incl += lane_ >= sh ? t : 0;
             }
             const uint64_t past = __ballot(incl > e);
             if (past != 0) {
                 const int l = __ffsll((unsigned long long)past) - 1;
                 const int n = __builtin_amdgcn_readlane(nb, l);
-                const int r = e - (__builtin_amdgcn_readlane(incl, l) - n * hs);
+                const int r = e - (__builtin_amdgcn_readlane(incl, l) - __builtin_amdgcn_readlane(own, l));
                 seq = base + l;
-                head = (r / n) * 8 + (int)(blockIdx.x & 7);
+                head = __builtin_amdgcn_readlane(h0, l) + (r / n) * 8;
                 qb_top = n - 1 - r % n;
                 break;
             }
             e -= __builtin_amdgcn_readlane(incl, 63);
         }
-        if (seq < 0 || head >= H) return;
+        if (seq < 0) return;
     } else if constexpr (FROM == kList) {
         // entry blockIdx / 8: sequence, group of 8 heads, query block; the
         // head within the group is blockIdx mod 8, the XCD the workgroup runs
@@ -509,8 +512,17 @@ hipError_t launch_attention_bf16(const uint16_t* q, const uint16_t* k, const uin
                            scale_log2, list);
         return hipGetLastError();
     };
-    // by query blocks where there is a list or few sequences to look through
-    const bool scan = list == nullptr && n_seq <= 128;
+    // By query blocks where there is a list, or, looked up among the sequences' lengths by
+    // each workgroup, where whole (sequence, head) pairs leave the chip idle or waiting for
+    // the longest: up to 1,500 pairs of up to three blocks or more, up to 330 of up to two
+    // (one block is the same work either way).  By pair / by blocks, us: 20 heads of 128,
+    // 9 prompts of 96 to 608 rows 33 / 17, 32 71 / 39, 64 87 / 78, 100 117 / 116; of 608
+    // rows all 9 71 / 49, 64 301 / 283, 100 459 / 446; 10 heads, 40 of 96 to 608 69 / 30, 200
+    // of 232 127 / 145; 4 heads, 40 of 232 23 / 20, 100 of 232 32 / 36.  (Before the pairs were
+    // dealt out, one XCD had a head: 40 prompts of 232 and 4 heads 30, 32 of 608 and 20 171.)
+    const int longest = n_prefix > max_seqlen - n_prefix ? n_prefix : max_seqlen - n_prefix;
+    const long long pairs = (long long)n_seq * n_heads;
+    const bool scan = list == nullptr && n_seq <= 128 && (longest > 2 * BQ ? pairs <= 1500 : longest > BQ && pairs <= 330);
     if (list != nullptr || scan) {
         if (!scan && (n_heads % 8 != 0 || n_list <= 0)) return hipErrorInvalidValue;
         const long long blocks = scan ? (long long)((n_heads + 7) / 8) * (T / BQ + n_seq) * 8 : (long long)n_list * 8;

@@ -81,9 +81,9 @@ hipError_t launch_gemm_swiglu(const uint16_t* a, const uint16_t* wg, const uint1
                               uint16_t* out, int M, int F, int K, hipStream_t st, bool reverse = false);
 
 // Varlen causal attention, bf16, head_dim hd (128 or 64).  q, k, v, o: [T][H*hd].
-// T rows in all.  With `list` (from launch_attention_worklist, n_list entries), or up
-// to 128 sequences, one workgroup runs one 128-query block; otherwise one workgroup
-// runs a whole sequence.
+// T rows in all.  With `list` (from launch_attention_worklist, n_list entries), or where
+// (sequence, head) pairs are few and long, one workgroup runs one 128-query block;
+// otherwise one workgroup runs a whole sequence.
 hipError_t launch_attention_bf16(const uint16_t* q, const uint16_t* k, const uint16_t* v,
                                  uint16_t* o, const int* cu, int n_seq, int T, int max_seqlen,
                                  int n_heads, int hd, int n_prefix, const int2* list, int n_list,

@@ -208,3 +208,39 @@ def test_hd64_attention_by_blocks_and_by_sequences(R, n_prefix):
     many = run(lens + [20, 0])                        # 129 or 130
     assert np.isfinite(few).all()
     assert np.array_equal(few, many[:len(few)])
+
+
+@pytest.mark.parametrize("H,hd,n_prefix,n", [(4, 64, 0, 100), (12, 64, 35, 90), (20, 64, 0, 70), (20, 64, 130, 9),
+                                             (2, 128, 0, 127), (10, 128, 300, 66), (18, 128, 0, 5)])
+def test_attention_blocks_dealt_to_all_heads(H, hd, n_prefix, n):
+    """Head counts that are not a multiple of 8, few enough pairs for attention by
+    query blocks; with as many more short sequences as it takes for whole ones:
+    the same rows, bit for bit."""
+    torch = torch_mod()
+    d, ffn = H * hd, 256
+    g = torch.Generator(device="cuda")
+    g.manual_seed(H + n)
+    mk = lambda *s, std=1.0, mean=0.0: torch.empty(*s, device="cuda", dtype=torch.bfloat16).normal_(mean, std, generator=g)
+    shape = dict(wq=(d, d), wk=(d, d), wv=(d, d), wo=(d, d), w_gate=(ffn, d), w_up=(ffn, d), w_down=(d, ffn))
+    W = {k: mk(*s, std=0.05) for k, s in shape.items()}
+    W["g_attn"], W["g_ffn"] = mk(d, std=0.05, mean=1.0), mk(d, std=0.05, mean=1.0)
+    import paper_2609_29029_amd as R
+    cfg = R.model_cfg(d, H, hd, ffn, 1, 1e-6, 10000.0, R.RIFT_BF16)
+    pre = [n_prefix] if n_prefix else []
+    own = ([400, 0, 1, 127, 128, 129, 257, 0, 300] + [(7 * i * i) % 290 for i in range(n)])[:n]
+    lens = pre + own
+    x = mk(sum(lens) + 400, d)
+
+    def run(lens):
+        cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        pos = np.concatenate([np.arange(l) + (n_prefix if i >= len(pre) else 0) for i, l in enumerate(lens)]).astype(np.int32)
+        T, L = int(cu[-1]), n_prefix + max(own)
+        ws = torch.empty(R.rift_prefill_workspace_size(cfg, T, L), dtype=torch.uint8, device="cuda")
+        hid = torch.empty(T, d, dtype=torch.float32, device="cuda")
+        R.rift_prefill(cfg, [W], x[:T], torch.from_numpy(cu).cuda(), torch.from_numpy(pos).cuda(), len(lens), L, hid, ws,
+                       n_prefix=n_prefix)
+        return hid
+
+    few = run(lens)
+    many = run(lens + [2] * 130)
+    assert torch.isfinite(few).all() and torch.equal(few, many[:len(few)])
