@@ -418,7 +418,9 @@ RIFT_API rift_status rift_prefill(const rift_model_cfg* cfg, const rift_layer_we
                          rift_stream stream);
 
 /*
- * rift_decode_workspace_size -- bytes of workspace for rift_decode_step.
+ * rift_decode_workspace_size -- bytes of workspace for rift_decode_step.  Not
+ * smaller for more prompts or longer ones, so one allocation made for the
+ * largest step serves the smaller ones.
  */
 RIFT_API size_t rift_decode_workspace_size(const rift_model_cfg* cfg, int32_t n_seq, int32_t max_seqlen,
                                            int32_t max_new);
